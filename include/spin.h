@@ -28,12 +28,14 @@
  *              stream) and returns before the GPU finishes.  Calls on one
  *              stream are ordered; calls from several host threads must use
  *              different streams.
- *   Graphs     the first inversion with a given entry point, mode, order,
+ *   Graphs     the second inversion with a given entry point, mode, order,
  *              leading dimensions, buffers and stream workspace records its
- *              launch sequence as a HIP graph; later identical calls replay it.  At
- *              most 64 graphs are kept (the cache is emptied when full, after
- *              waiting for the device).  The environment variable
- *              SPIN_NO_GRAPH=1 makes every call launch its kernels directly.
+ *              launch sequence as a HIP graph and later identical calls replay
+ *              it; the first one, and schedules of a few steps, launch their
+ *              kernels directly.  At most 64 graphs are kept (the cache is
+ *              emptied when full, after waiting for the device).  The
+ *              environment variable SPIN_NO_GRAPH=1 makes every call launch
+ *              its kernels directly.
  *   Leaves     two further environment variables change how a leaf is
  *              eliminated but never its result: SPIN_NO_SPEC=1 runs the pivot
  *              search at every step instead of first trying the diagonal

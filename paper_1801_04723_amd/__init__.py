@@ -283,7 +283,7 @@ def _empty_like_layout(a, order):
     import torch
     n = a.shape[0]
     if order == "F":
-        return torch.empty((n, n), dtype=torch.float64, device=a.device).t().contiguous().t()
+        return torch.empty_strided((n, n), (1, n), dtype=torch.float64, device=a.device)
     return torch.empty((n, n), dtype=torch.float64, device=a.device)
 
 

@@ -444,7 +444,7 @@ constexpr int kNoSpecKey = 1 << 12;
 void drop_graphs_for(void *base) {
     for (auto it = g_graphs.begin(); it != g_graphs.end();) {
         if (std::get<7>(it->first) == base) {
-            hipGraphExecDestroy(it->second);
+            if (it->second) hipGraphExecDestroy(it->second);
             it = g_graphs.erase(it);
         } else {
             ++it;
@@ -601,25 +601,52 @@ int hip_fail(hipError_t e) {
     return e == hipErrorOutOfMemory ? SPIN_E_NOMEM : SPIN_E_HIP;
 }
 
-// Enqueue `body(stream)` either directly or through a cached graph.
+// Schedule steps below which a call is never captured: hipGraphLaunch costs the
+// host about 15 us, a plain launch 3 to 5 us, and the first kernel of a graph
+// starts about 10 us later (one order-64 leaf, two launches: 20 us a call in a
+// row and 36 us alone launched directly, 28 and 47 us as a graph; order 256 at
+// leaf 64, 16 steps: 134 us both ways, and 21 us less host time as a graph).
+constexpr size_t kGraphMinSteps = 8;
+
+// Enqueue `body(stream)` either directly or through a cached graph.  A key's
+// first call is launched directly and only remembered (an entry without a
+// graph): capture and instantiation cost 1 to 3 us per launch (order 2048 at
+// leaf 128: 1.64 ms for a first call with capture, 1.46 ms without), which a
+// caller with new buffers on every call would never get back.  The second
+// call with the same key captures.  On a stream that is itself being captured
+// the graph is launched as before.
 template <typename F>
 int run_maybe_graph(const std::tuple<int, int64_t, int64_t, int64_t, int64_t, const void *, void *,
                                      void *, int> &key,
-                    hipStream_t s, F body) {
-    if (!graphs_enabled()) {
+                    hipStream_t s, size_t steps, F body) {
+    auto direct = [&]() -> int {
         hipError_t e = body(s);
         return e == hipSuccess ? SPIN_OK : hip_fail(e);
-    }
+    };
+    if (!graphs_enabled()) return direct();
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+    const bool capturing = cap != hipStreamCaptureStatusNone;
+    if (steps < kGraphMinSteps && !capturing) return direct();
     auto it = g_graphs.find(key);
     if (it == g_graphs.end() && g_graphs.size() >= kMaxGraphs) {
         // bounded cache: callers that cycle through many buffers must not grow
-        // it without limit.  Wait for every launch, then drop all graphs; they
-        // are captured again on their next use.
-        if (hipDeviceSynchronize() != hipSuccess) return hip_fail(hipErrorUnknown);
-        for (auto &kv : g_graphs) hipGraphExecDestroy(kv.second);
-        g_graphs.clear();
+        // it without limit.  Entries without a graph go first; otherwise wait
+        // for every launch, then drop all graphs; they are captured again on
+        // their next uses.
+        for (auto e = g_graphs.begin(); e != g_graphs.end();) e = e->second ? std::next(e) : g_graphs.erase(e);
+        if (g_graphs.size() >= kMaxGraphs) {
+            if (hipDeviceSynchronize() != hipSuccess) return hip_fail(hipErrorUnknown);
+            for (auto &kv : g_graphs) hipGraphExecDestroy(kv.second);
+            g_graphs.clear();
+        }
     }
-    if (it == g_graphs.end()) {
+    if (it == g_graphs.end() && !capturing) {
+        const int rc = direct();
+        if (rc == SPIN_OK) g_graphs.emplace(key, nullptr);
+        return rc;
+    }
+    if (it == g_graphs.end() || !it->second) {
         if (!g_capture && hipStreamCreateWithFlags(&g_capture, hipStreamNonBlocking) != hipSuccess)
             return hip_fail(hipErrorUnknown);
         if (hipStreamBeginCapture(g_capture, hipStreamCaptureModeThreadLocal) != hipSuccess)
@@ -635,7 +662,7 @@ int run_maybe_graph(const std::tuple<int, int64_t, int64_t, int64_t, int64_t, co
         e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
         hipGraphDestroy(graph);
         if (e != hipSuccess) return hip_fail(e);
-        it = g_graphs.emplace(key, exec).first;
+        it = g_graphs.insert_or_assign(key, exec).first;
     }
     hipError_t e = hipGraphLaunch(it->second, s);
     return e == hipSuccess ? SPIN_OK : hip_fail(e);
@@ -700,7 +727,7 @@ int spin_invert(const double *A, int64_t n, int64_t lda, double *Ainv, int64_t l
     };
     return run_maybe_graph(std::make_tuple(spec ? 0 : kNoSpecKey, n, lda, ldx, leaf, (const void *)A, (void *)Ainv,
                                            (void *)w->base, 0),
-                           s, body);
+                           s, P.ops.size(), body);
 }
 
 int spin_invert_spd(const double *A, int64_t n, int64_t lda, double *Ainv, int64_t ldx,
@@ -726,7 +753,7 @@ int spin_invert_spd(const double *A, int64_t n, int64_t lda, double *Ainv, int64
     };
     return run_maybe_graph(std::make_tuple(spec ? 2 : 2 + kNoSpecKey, n, lda, ldx, leaf, (const void *)A, (void *)Ainv,
                                            (void *)w->base, 0),
-                           s, body);
+                           s, P.ops.size(), body);
 }
 
 int spin_invert_lu(const double *A, int64_t n, int64_t lda, double *Ainv, int64_t ldx,
@@ -753,7 +780,7 @@ int spin_invert_lu(const double *A, int64_t n, int64_t lda, double *Ainv, int64_
     };
     return run_maybe_graph(std::make_tuple(spec ? 3 : 3 + kNoSpecKey, n, lda, ldx, leaf, (const void *)A, (void *)Ainv,
                                            (void *)w->base, 0),
-                           s, body);
+                           s, P.ops.size(), body);
 }
 
 int spin_invert_mixed(const double *A, int64_t n, int64_t lda, double *Ainv, int64_t ldx,
@@ -861,7 +888,7 @@ int spin_invert_mixed(const double *A, int64_t n, int64_t lda, double *Ainv, int
     };
     rc = run_maybe_graph(std::make_tuple(1 + 16 * mode + (spec ? 0 : kNoSpecKey), n, lda, ldx, leaf, (const void *)A,
                                          (void *)Ainv, (void *)base, ns_steps),
-                         s, body);
+                         s, P.ops.size(), body);
     if (rc || !rep) return rc;
 
     // Report: residual of the unrefined and of the final inverse.  With
@@ -1032,7 +1059,8 @@ const char *spin_strerror(int code) {
 void spin_release(void) {
     std::lock_guard<std::mutex> lk(g_mu);
     hipDeviceSynchronize();
-    for (auto &kv : g_graphs) hipGraphExecDestroy(kv.second);
+    for (auto &kv : g_graphs)
+        if (kv.second) hipGraphExecDestroy(kv.second);
     g_graphs.clear();
     for (auto &kv : g_ws)
         if (kv.second.base) hipFree(kv.second.base);
