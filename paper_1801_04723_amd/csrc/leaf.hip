@@ -25,20 +25,22 @@
 //   (E = unit entries at the pivot rows) and the pivot rows Q of the other
 //   columns; those columns are then updated by one grouped matrix-core
 //   product  Z[:, out] += U' * Q.  A final pass writes the permuted result.
-//   Up to order 512 the panel's search kernel is the same 2-D kernel, its
-//   speculative elimination a column-block kernel, and an FP64 leaf is not
-//   copied first: the first panel and its product read the leaf's input in
-//   place.  Above 512 a rotating-slot panel kernel works on narrower panels
+//   Up to order 512 the panel's kernel is the same as for whole leaves (full
+//   panels of leaves of order 129 .. 256: two workgroups, leaf_duo), and an
+//   FP64 leaf is not copied first: the first panel and its product read the
+//   leaf's input in place.  Above 512 a rotating-slot panel kernel works on narrower panels
 //   and the input is copied into Z.
 //
-// Speculation: every kernel up to order 512 first tries the diagonal pivots,
-// checks each choice exactly and falls back to its search when a check fails
-// (gj2d_any); the result is the search's bit for bit either way.
+// Speculation: every kernel up to order 512 first tries the diagonal pivots
+// in 16-step blocks on the matrix cores, checks each choice exactly and falls
+// back to its search when a check fails (gj2d_any, gj_blocked); the result is
+// the search's bit for bit either way.
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
 #include <climits>
 #include <cstdlib>
+#include <utility>
 
 #include "spin_kernels.hpp"
 
@@ -129,20 +131,29 @@ struct LeafArgs {
     int duo_spin;
 };
 
+// LDS of gj2d_run, in doubles (shared with the blocked tier, which runs first).
+template <int TR, int RR, int RC>
+struct RunLds {
+    static constexpr int kL = TR * RR, kB = 16 * RC;
+    static constexpr int oF = 2 * kL, oRow = oF + 2 * kL, oInt = oRow + 2 * kB;
+    static constexpr int kDoubles = oInt + (kL + kB + 1) / 2;
+};
+
 template <int TR, int RR, int RC, bool WHOLE, typename TI, typename TO>
-__device__ __attribute__((always_inline)) inline void gj2d_run(const LeafArgs &a) {
+__device__ __attribute__((always_inline)) inline void gj2d_run(const LeafArgs &a, double *sm) {
     constexpr int NT = 16 * TR;
     constexpr int LMAX = TR * RR;
     constexpr int NBMAX = 16 * RC;
     constexpr int CPL = LMAX / 64;
     static_assert(CPL * 64 == LMAX, "rows must cover whole waves");
-    __shared__ double colbuf[2][LMAX];
+    using S = RunLds<TR, RR, RC>;
+    double(*const colbuf)[LMAX] = reinterpret_cast<double(*)[LMAX]>(sm);
     // Panels: the multipliers, i.e. column c with 0 at the pivot row (the
     // pivot row is scaled in place instead), so the update needs no select.
-    __shared__ double fbuf[2][LMAX];
-    __shared__ double rowbuf[2][NBMAX];
-    __shared__ int pivstep[LMAX];  // step at which a row was the pivot, or -1
-    __shared__ int prow_s[NBMAX];  // pivot row of each step
+    double(*const fbuf)[LMAX] = reinterpret_cast<double(*)[LMAX]>(sm + S::oF);
+    double(*const rowbuf)[NBMAX] = reinterpret_cast<double(*)[NBMAX]>(sm + S::oRow);
+    int *const pivstep = reinterpret_cast<int *>(sm + S::oInt);  // step at which a row was the pivot, or -1
+    int *const prow_s = pivstep + LMAX;                          // pivot row of each step
     // Thread t holds rows tr + TR r of columns tc + 16 q.  Whole leaves put
     // the 16 threads of a row group in one wave (t = 16 tr + tc), so one wave
     // publishes the pivot row.  Panels put TR consecutive rows of one column
@@ -340,7 +351,7 @@ __device__ __attribute__((always_inline)) inline void gj2d_run(const LeafArgs &a
     if (t == 0 && bad) atomicMin(a.status, a.col0 + k0 + bad);
 }
 
-// ------------------------------------------ speculative whole-leaf kernel ---
+// --------------------------------------------- blocked speculative tier ---
 // The elimination of gj2d_run for blocks whose partial-pivoting choice at
 // step k is row k itself, as it is at every step for strictly diagonally
 // dominant blocks (their Schur complements stay dominant) and, in practice,
@@ -349,519 +360,474 @@ __device__ __attribute__((always_inline)) inline void gj2d_run(const LeafArgs &a
 // finite and nonzero and no unused row holds a larger magnitude or a
 // non-finite value.  As long as every earlier step stood, the unused rows are
 // exactly the rows below the pivot, so a tie goes to the pivot row, which is
-// what the search's smallest-index rule picks.
+// what the search's smallest-index rule picks.  The outputs are written only
+// when every check passed.
 //
-// With the pivot row known in advance the search leaves the dependent chain,
-// and so does one barrier: once step c is applied, the owners of column c+1
-// publish its multipliers and the owners of row c+1 (one wave, which also
-// holds the pivot) the scaled pivot row, and after one barrier every thread
-// applies step c+1.  Every element goes through the same operations as in
-// gj2d_run (the same division, products and fused multiply-adds), so when
-// every check passes the outputs are gj2d_run's bit for bit.  They are written
-// only then.  Returns whether every check passed (the same in every thread);
-// on false nothing has been written.  Whole leaves only (panels have their
-// own kernels below).
-template <int TR, int RR, int RC, typename TI, typename TO>
-__device__ __attribute__((always_inline)) inline bool gj2d_spec(const LeafArgs &a) {
-    constexpr int LMAX = TR * RR;
-    constexpr int NBMAX = 16 * RC;
-    static_assert(TR == 16 || TR == 32, "row groups of 16 or 32 threads");
-    // Shared arrays are indexed by register slot, not by row: entry tr + TR r
-    // belongs to slot r of the threads with that tr (the same map in every
-    // thread), so that every access is a per-thread base plus a constant.
-    __shared__ double fbs[2][LMAX];   // multipliers of a step, -1 at its pivot row
-    __shared__ double rws[2][NBMAX];  // its scaled pivot row
-    __shared__ double pvs[2];         // |pivot|
-    const int t = threadIdx.x, wave = t >> 6;
-    const int tr = t >> 4, tc = t & 15;
-    const int L = a.L;
+// With the pivot rows known in advance, 16 steps form one block step on the
+// matrix cores.  v_mfma_f64_16x16x4f64 adds its four products to each element
+// as a chain of fused multiply-adds in ascending k (checked against fma() on
+// random and subnormal operands), so four of them apply 16 steps to a 16 x 16
+// block with the very operations, in the very order, of gj2d_run's sixteen
+// rank-1 updates, and the result is the search's bit for bit.  Block step b
+// on the 16 columns / rows Kb:
+//   diagonal  one wave runs the 16 steps on the 16 x 16 diagonal block, the
+//             only serial chain: a reciprocal, a product and a fused
+//             multiply-add per step, the pivot row and column passed between
+//             lanes by DPP and lane swaps;
+//   panels    one lane per row takes the 16 steps through the columns Kb
+//             (its multipliers F; they are checked here), one lane per column
+//             takes them through the rows Kb (the scaled pivot rows R);
+//   update    every other 16 x 16 block takes four MFMAs with -F and R.
+// The block lives in the accumulators of NW waves (wave w holds the row
+// blocks w + NW i) and only panels pass through LDS.  While the update runs,
+// the wave that holds the next diagonal block updates that one first and goes
+// straight into its chain.
+//
+// What bounds it: FP64 vector and matrix instructions share one unit per
+// SIMD, and a block step of a 128-order leaf spends about 12 000 cycles there
+// on the busiest one: panels 3 100 (16 x 24 instructions of a lone wave), the
+// chain 5 000 (16 x 37 dependent instructions), the MFMAs of the two waves on
+// the chain's SIMD about 3 500.  Placing the chain wave's own MFMAs between
+// its steps gained nothing for the same reason.  Whole inversions of one leaf
+// (launches included), against the earlier kernels with a barrier or a flag
+// per step: order 64 30 -> 20 us, 128 88 -> 50 us, 257 325 -> 247 us, 512
+// 758 -> 547 us; full panels of orders 129 .. 256 stay with leaf_duo, whose
+// two CUs take 29 us against 34 us here (22 us of steps, the rest loads and
+// stores of one CU).
+typedef double d4_t __attribute__((ext_vector_type(4)));
 
-    double z[RR][RC];
-#pragma unroll
-    for (int r = 0; r < RR; ++r)
-#pragma unroll
-        for (int q = 0; q < RC; ++q) {
-            const int row = tr + TR * r, col = tc + 16 * q;
-            z[r][q] = (row < L && col < L) ? (double)static_cast<const TI *>(a.in)[row + (int64_t)col * a.ldi]
-                                           : 0.0;
-        }
-    bool viol = false;
-    double *const fbt = &fbs[0][tr];
-    double *const rwt = &rws[0][tc];
+template <int NW, int RB, int NC>
+struct BlkLds {
+    static constexpr int kRows = 16 * NW * RB, kCols = 16 * NC;
+    // two panel buffers where 160 KB hold them: the panels of the next block
+    // step are then written while the current ones are still read
+    static constexpr bool kTwo = NW * RB <= 16;
+    static constexpr int kBufs = kTwo ? 2 : 1;
+    // pitches that spread the 16 x 4 element accesses of a wave over the banks
+    static constexpr int kFLd = kRows + 16, kPrLd = kCols + 4, kRLd = kCols + 16;
+    static constexpr int oPc = 0;                        // column panel [16][kFLd], per buffer
+    static constexpr int oF = oPc + kBufs * 16 * kFLd;   // F [16][kFLd]
+    static constexpr int oPr = oF + 16 * kFLd;           // row panel [16][kPrLd], per buffer
+    static constexpr int oR = oPr + kBufs * 16 * kPrLd;  // R [16][kRLd]
+    static constexpr int oDr = oR + 16 * kRLd;           // pivot rows inside the diagonal block
+    static constexpr int oDm = oDr + 256;                // its active columns
+    static constexpr int oDump = oDm + 256;              // unwanted stores of the chain
+    static constexpr int kDoubles = oDump + 16 * 15 + 16;
+};
 
-    // One step c = 16 cb + cc, LDS buffer B = c & 1: publication (its column
-    // and pivot row are final once step c - 1 is applied), one barrier, the
-    // check and the update.  cb and B are constants after unrolling.
-    auto step = [&](const int cb, const int cc, const int B) {
-        const int PR = (16 * cb) / TR;       // register slot of the pivot row
-        const int pt = (16 * cb) % TR + cc;  // its owners' tr
-        // the 16 owners of row c are lanes 16 pt .. 16 pt + 15 of one wave
-        if (wave == (16 * pt) >> 6) {
-            const double piv = readlane_f64(z[PR][cb], (16 * pt + cc) & 63);
-            if (tr == pt) {
-                const double pinv = 1.0 / piv;
+// The same value, unknown to the compiler: what is computed from it (lane
+// masks, addresses) is computed anew and not held in registers across loops.
+__device__ inline int opaque(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// Ends a branch taken for one of several register blocks.  Without it the
+// compiler merges the branches' common ends into one with a run-time index,
+// which puts the indexed registers into scratch memory.
+template <int I>
+__device__ __attribute__((always_inline)) inline void branch_end() {
+    asm volatile("; block %0" ::"n"(I));
+}
+
+// f(0), ..., f(N - 1) with constant arguments.
+template <typename F, int... I>
+__device__ __attribute__((always_inline)) inline void static_for_seq(F f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __attribute__((always_inline)) inline void static_for(F f) {
+    static_for_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// x[j] = fma(-f, r of lane j, x[j]) for all 16 j, the lane within each group
+// of 16 (DPP row_newbcast).  The wait states before the first DPP read cover
+// a vector write of r just before it.
+__device__ inline void fmac_rows(double (&x)[16], double r, double f) {
+#define SPIN_FMAC(J) "v_fmac_f64_dpp %" #J ", %16, -%17 row_newbcast:" #J " row_mask:0xf bank_mask:0xf\n\t"
+    asm("s_nop 1\n\t" SPIN_FMAC(0) SPIN_FMAC(1) SPIN_FMAC(2) SPIN_FMAC(3) SPIN_FMAC(4) SPIN_FMAC(5) SPIN_FMAC(6)
+            SPIN_FMAC(7) SPIN_FMAC(8) SPIN_FMAC(9) SPIN_FMAC(10) SPIN_FMAC(11) SPIN_FMAC(12) SPIN_FMAC(13)
+                SPIN_FMAC(14) SPIN_FMAC(15)
+        : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7]),
+          "+v"(x[8]), "+v"(x[9]), "+v"(x[10]), "+v"(x[11]), "+v"(x[12]), "+v"(x[13]), "+v"(x[14]), "+v"(x[15])
+        : "v"(r), "v"(f));
+#undef SPIN_FMAC
+}
+
+// The value of lane K of each lane's own group of 16.
+template <int K>
+__device__ inline double row_bcast(double x) {
+    return __builtin_amdgcn_update_dpp(0.0, x, 0x150 + K, 0xf, 0xf, true);
+}
+
+// Pivots whose reciprocal the chain forms without the scaling and fix-up of
+// the FP64 division: for these the division leaves divisor and quotient
+// unscaled, so the bits are the same.  Others (zero and non-finite pivots
+// among them) fail the block's check.
+__device__ inline bool plain_pivot(double x) {
+    const unsigned e = (unsigned)(__double_as_longlong(x) >> 52) & 0x7ffu;
+    return e - 523u <= 1000u;  // |x| in 2^-500 .. 2^501
+}
+
+// Step K of the 16 x 16 diagonal block: lane l holds row l % 16 of columns
+// 4 v + l / 16.
+//   - the active column (group K % 4 of D[K / 4]) passes through LDS, where
+//     its values, the step's multipliers with the pivot at row K, are kept
+//     for the panels; it restarts as the unit column;
+//   - 1 / pivot: reciprocal estimate, two Newton steps and the division's
+//     final correction, in every lane (lane (K % 4, K) holds the pivot);
+//   - the pivot row (lane K of each group) is scaled in place, published, and
+//     reaches the other rows by DPP inside the multiply-add; its own
+//     multiplier is 0.
+// A lone wave issues an instruction about every five to nine cycles, so the
+// step has no branch: lanes whose store is not wanted store to a dump area.
+// The step's stores go to dm + 16 K + (row) and dr + 16 K + (column).
+template <int K>
+__device__ __attribute__((always_inline)) inline void diag_step(d4_t &D, int rr, int g, double *dm, double *dr,
+                                                                double *dump) {
+    constexpr int V = K / 4, G = K % 4;
+    const double x = D[V];
+    double *const pm = (g == G ? dm : dump) + rr;
+    pm[16 * K] = x;
+    // the other groups read what this group wrote: LDS serves a wave's accesses
+    // in order, the fences keep the compiler's order too
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    double f = dm[16 * K + rr];
+    __builtin_amdgcn_sched_barrier(0);  // the read goes out before the arithmetic
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(y, fma(-x, y, 1.0), y);
+    y = fma(y, fma(-x, y, 1.0), y);
+    y = fma(fma(-x, y, 1.0), y, y);
+    const double pinv = readlane_f64(y, 16 * G + K);
+    const bool prow = rr == K;
+    const double unit = prow ? 1.0 : 0.0;
+    D[V] = g == G ? unit : x;
+    const double sc = prow ? pinv : 1.0;
+    double *const pr = (prow ? dr : dump) + g;
 #pragma unroll
-                for (int q = 0; q < RC; ++q) {
-                    rwt[B * NBMAX + 16 * q] = (q == cb && tc == cc) ? pinv : z[PR][q] * pinv;
-                    z[PR][q] = 0.0;  // the update adds the scaled row (multiplier -1)
+    for (int v = 0; v < 4; ++v) {
+        D[v] *= sc;
+        pr[16 * K + 4 * v] = D[v];
+    }
+    f = prow ? 0.0 : f;
+    // D[v] = fma(-f, D[v] of lane K, D[v])
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %0, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %1, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %2, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %3, -%4 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+        : "+v"(D[0]), "+v"(D[1]), "+v"(D[2]), "+v"(D[3])
+        : "v"(f), "n"(K));
+}
+
+template <int... K>
+__device__ __attribute__((always_inline)) inline void diag_chain(d4_t &D, int lane, double *dm, double *dr,
+                                                                 double *dump, std::integer_sequence<int, K...>) {
+    lane = opaque(lane);
+    (diag_step<K>(D, lane & 15, lane >> 4, dm, dr, dump), ...);
+}
+
+// The 16 steps on one row of the block column (x: its 16 columns): F gets the
+// multipliers (pitch ld).  Returns whether a checked row holds a candidate
+// larger than a pivot or not finite.
+template <int... K>
+__device__ __attribute__((always_inline)) inline bool row_steps(double (&x)[16], const double *dr16, double pd,
+                                                                double *F, int ld, std::integer_sequence<int, K...>) {
+    bool bad = false;
+    double r[16] = {dr16[16 * K]...};  // loaded before the stores to F, which the compiler keeps in order
+    (
+        [&] {
+            const double f = x[K];
+            F[K * ld] = f;
+            bad = bad | !(fabs(f) <= fabs(row_bcast<K>(pd)));
+            x[K] = 0.0;
+            fmac_rows(x, r[K], f);
+        }(),
+        ...);
+    return bad;
+}
+
+// The 16 steps on one column of the block row (y: its 16 rows): R gets the
+// scaled pivot rows' entries (pitch ld).
+template <int... K>
+__device__ __attribute__((always_inline)) inline void col_steps(double (&y)[16], const double *dm16, double id,
+                                                                double *R, int ld, std::integer_sequence<int, K...>) {
+    double m[16] = {dm16[16 * K]...};
+    (
+        [&] {
+            const double r = y[K] * row_bcast<K>(id);
+            R[K * ld] = r;
+            fmac_rows(y, m[K], r);
+            y[K] = r + 0.0;
+        }(),
+        ...);
+}
+
+template <int NW, int RB, int NC, bool WHOLE, typename TI, typename TO>
+__device__ __attribute__((always_inline)) inline bool gj_blocked(const LeafArgs &a, double *sm) {
+    using S = BlkLds<NW, RB, NC>;
+    constexpr int NT = 64 * NW;
+    const int t = threadIdx.x, lane0 = t & 63, lane = lane0, rr = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int L = a.L, k0 = WHOLE ? 0 : a.k0, nb = WHOLE ? a.L : a.nb;
+    if ((k0 & 15) != 0 || nb < 1 || nb > S::kCols || L > S::kRows) return false;  // the same in every thread
+    const double *src = WHOLE ? nullptr : (a.in ? static_cast<const double *>(a.in) : a.Z);
+    const int64_t lds = WHOLE ? 0 : (a.in ? a.ldi : a.ldz);
+
+    // lane l holds row 16 (w + NW i) + l % 16 of columns 16 c + 4 v + l / 16
+    d4_t acc[RB][NC];
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = 16 * (w + NW * i) + rr, col = 16 * c + 4 * v + g;
+                // beyond the last step the block continues as the identity: its
+                // steps leave every other value as it is
+                double x = (col >= nb && row == k0 + col) ? 1.0 : 0.0;
+                if (row < L && col < nb) {
+                    if (WHOLE)
+                        x = (double)static_cast<const TI *>(a.in)[row + (int64_t)col * a.ldi];
+                    else
+                        x = src[row + (int64_t)(k0 + col) * lds];
                 }
-                if (tc == cc) pvs[B] = fabs(piv);
+                acc[i][c][v] = x;
             }
-        }
-        if (tc == cc) {
-#pragma unroll
-            for (int r = 0; r < RR; ++r) {
-                fbt[B * LMAX + TR * r] = (r == PR && tr == pt) ? -1.0 : z[r][cb];
-                z[r][cb] = 0.0;
-            }
-        }
-        __syncthreads();
-        double f[RR], rv[RC];
-#pragma unroll
-        for (int r = 0; r < RR; ++r) f[r] = fbt[B * LMAX + TR * r];
-#pragma unroll
-        for (int q = 0; q < RC; ++q) rv[q] = rwt[B * NBMAX + 16 * q];
-        // check of step c: the pivot, then the unused rows of this thread
-        const double apiv = pvs[B];
-        bool v = !(apiv > 0.0) || !(apiv <= DBL_MAX);
-#pragma unroll
-        for (int r = 0; r < RR; ++r) {
-            if (r < PR) continue;  // rows before the pivot: used
-            const bool used = (r == PR) && (tr <= pt);
-            v = v || (!used && !(fabs(f[r]) <= apiv));
-        }
-        viol = viol || v;
-#pragma unroll
-        for (int r = 0; r < RR; ++r)
-#pragma unroll
-            for (int q = 0; q < RC; ++q) z[r][q] = fma(-f[r], rv[q], z[r][q]);
-    };
-
-#pragma unroll
-    for (int cb = 0; cb < RC; ++cb) {
-        for (int cc = 0; cc < 16; cc += 2) {
-            if (16 * cb + cc >= L) break;
-            step(cb, cc, 0);
-            if (16 * cb + cc + 1 >= L) break;
-            step(cb, cc + 1, 1);
-        }
-    }
-    if (__syncthreads_or(viol)) return false;
-
-    TO *out = static_cast<TO *>(a.out);
-#pragma unroll
-    for (int r = 0; r < RR; ++r)
-#pragma unroll
-        for (int q = 0; q < RC; ++q) {
-            const int row = tr + TR * r, col = tc + 16 * q;
-            if (row < L && col < L) out[row + (int64_t)col * a.ldo] = (TO)z[r][q];
-        }
-    return true;
-}
-
-// -------------------------------------- speculative column-block panel ---
-// The speculative elimination of a panel (nb <= 64 columns from k0, a
-// multiple of 64, L <= 64 RR rows) with one barrier per column block instead
-// of one per step.  Each of the NW waves holds CW = 64 / NW panel columns in
-// full: lane l, slot i of wave w holds row l + 64 ((i + rot) mod RR),
-// rot = k0 / 64, of columns CW w .. CW w + CW - 1, so the pivot row k0 + c of
-// step c sits in slot 0 of lane c and the multipliers of step c are one
-// column of a single wave.  Wave s runs the steps of its own columns alone,
-// taking the pivot row from lane c with readlane, and publishes each step's
-// multipliers, pivot and inverse pivot; after one barrier every other wave
-// applies those steps to its own columns, the pivot row again read from its
-// lane c, and wave s + NW/2 checks them against every unused row.  Wave s + 1
-// has then applied every earlier step to its columns and runs its own; it is
-// the critical path and runs at raised issue priority meanwhile.
-// Each element goes through the operations of gj2d_run in the same order
-// (the pivot row scaled by the inverse pivot, the multipliers taken before
-// the step, the pivot column restarting from 0, one fused multiply-add per
-// step), so when every pivot check passes the outputs are gj2d_run's bit for
-// bit.  Returns whether every check passed; on false nothing is written.
-// Used for panels of 257 .. 512 rows; smaller ones take wpanel_pipe below.
-template <int RR, int NW>
-__device__ __attribute__((always_inline)) inline bool wpanel_spec(const LeafArgs &a) {
-    constexpr int NT = 64 * NW, CW = 64 / NW;  // threads, columns per wave
-    static_assert(CW * NW == 64, "the waves cover 64 columns");
-    __shared__ double fpub[2][RR][CW][64];  // multipliers of a column block's steps
-    __shared__ double ppub[2][2][CW];       // their inverse pivots and pivots
-    const int t = threadIdx.x, lane = t & 63;
-    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int L = a.L, k0 = a.k0, nb = a.nb;
-    const double *src = a.in ? static_cast<const double *>(a.in) : a.Z;
-    const int64_t lds = a.in ? a.ldi : a.ldz;
-    const int rot = k0 >> 6;
-    bool viol = (k0 & 63) != 0 || L > 64 * RR || nb > 64 || nb < 1;
-    if (viol) return false;  // the same in every thread
-    int rowr[RR];
-    int rel[RR];  // row - k0 for rows inside the leaf from k0 on, else -1
-#pragma unroll
-    for (int i = 0; i < RR; ++i) {
-        rowr[i] = lane + 64 * ((i + rot) % RR);
-        rel[i] = (i + rot < RR && rowr[i] < L) ? lane + 64 * i : -1;
-    }
-    double z[RR][CW];
-#pragma unroll
-    for (int i = 0; i < RR; ++i)
-#pragma unroll
-        for (int j = 0; j < CW; ++j) {
-            const int col = CW * w + j;
-            z[i][j] = (rowr[i] < L && col < nb) ? src[rowr[i] + (int64_t)(k0 + col) * lds] : 0.0;
-        }
-    // the rows before the panel must be the used ones and no other
-    if (w == 0 && k0 > 0) {
-#pragma unroll
-        for (int i = 0; i < RR; ++i)
-            if (rowr[i] < L && ((a.used[rowr[i]] != 0) != (rowr[i] < k0))) viol = true;
-    }
-
-    // Step c = 8w + j on the wave's own columns (j a constant after
-    // unrolling); no branch, so that consecutive steps overlap.
-    auto own_step = [&](const int j, const int B) {
-        const int c = CW * w + j;
-        const double piv = readlane_f64(z[0][j], c);
-        const double pinv = 1.0 / piv;
-        const bool pl = lane == c;
-        double rv[CW], f[RR];
-#pragma unroll
-        for (int jj = 0; jj < CW; ++jj) rv[jj] = (jj == j) ? pinv : readlane_f64(z[0][jj], c) * pinv;
-#pragma unroll
-        for (int i = 0; i < RR; ++i) {
-            f[i] = (i == 0 && pl) ? 0.0 : z[i][j];
-            fpub[B][i][j][lane] = f[i];
-        }
-        if (lane == 0) {
-            ppub[B][0][j] = pinv;
-            ppub[B][1][j] = piv;
-        }
-        // the pivot row (multiplier 0) restarts from the scaled row, the
-        // pivot column from 0
-#pragma unroll
-        for (int i = 0; i < RR; ++i)
-#pragma unroll
-            for (int jj = 0; jj < CW; ++jj) {
-                double base = (jj == j) ? 0.0 : z[i][jj];
-                if (i == 0) base = pl ? rv[jj] : base;
-                z[i][jj] = fma(-f[i], rv[jj], base);
-            }
-    };
-    // Step c = 8s + j of another wave's block, applied to this wave's columns,
-    // with the step's multipliers f and inverse pivot pinv already loaded.
-    auto replay_step = [&](const int s, const int j, const double (&f)[RR], const double pinv) {
-        const int c = CW * s + j;
-        const bool pl = lane == c;
-        double rv[CW];
-#pragma unroll
-        for (int jj = 0; jj < CW; ++jj) rv[jj] = readlane_f64(z[0][jj], c) * pinv;
-#pragma unroll
-        for (int i = 0; i < RR; ++i)
-#pragma unroll
-            for (int jj = 0; jj < CW; ++jj) z[i][jj] = fma(-f[i], rv[jj], z[i][jj]);
-        if (pl) {
-#pragma unroll
-            for (int jj = 0; jj < CW; ++jj) z[0][jj] = fma(-0.0, rv[jj], rv[jj]);
-        }
-    };
-    // A block's replay reads each step's multipliers one step ahead, so the
-    // LDS latency overlaps the previous step's update.
-    auto replay_block = [&](const int s, const int B) {
-        double fc[RR], pc = ppub[B][0][0];
-#pragma unroll
-        for (int i = 0; i < RR; ++i) fc[i] = fpub[B][i][0][lane];
-#pragma unroll
-        for (int j = 0; j < CW; ++j) {
-            if (CW * s + j >= nb) break;
-            double fn[RR], pn = 0.0;
-            if (j + 1 < CW) {
-                pn = ppub[B][0][j + 1];
-#pragma unroll
-                for (int i = 0; i < RR; ++i) fn[i] = fpub[B][i][j + 1][lane];
-            }
-            replay_step(s, j, fc, pc);
-            if (j + 1 < CW) {
-                pc = pn;
-#pragma unroll
-                for (int i = 0; i < RR; ++i) fc[i] = fn[i];
-            }
-        }
-    };
-    // The checks of block s: each pivot finite and nonzero, and no unused row
-    // (rel > c; the pivot row's published multiplier is 0) larger in
-    // magnitude or not finite.
-    auto check_block = [&](const int s, const int B) {
-        bool v = false;
-#pragma unroll
-        for (int j = 0; j < CW; ++j) {
-            const int c = CW * s + j;
-            if (c >= nb) break;
-            const double apiv = fabs(ppub[B][1][j]);
-            v = v || !(apiv > 0.0) || !(apiv <= DBL_MAX);
-#pragma unroll
-            for (int i = 0; i < RR; ++i) v = v || (rel[i] > c && !(fabs(fpub[B][i][j][lane]) <= apiv));
-        }
-        viol = viol || v;
-    };
-
-    const int nblk = (nb + CW - 1) / CW;
-    for (int s = 0; s < nblk; ++s) {
-        const int B = s & 1;
-        if (w == s) {
-#pragma unroll
-            for (int j = 0; j < CW; ++j)
-                if (CW * s + j < nb) own_step(j, B);
-            __builtin_amdgcn_s_setprio(0);
-        }
-        __syncthreads();
-        if (w == s + 1) __builtin_amdgcn_s_setprio(2);
-        if (w != s && CW * w < nb) replay_block(s, B);
-        if (w == (s + NW / 2) % NW) check_block(s, B);
-    }
-    if (__syncthreads_or(viol)) return false;
-
-#pragma unroll
-    for (int i = 0; i < RR; ++i)
-#pragma unroll
-        for (int j = 0; j < CW; ++j) {
-            const int row = rowr[i], col = CW * w + j;
-            if (row < L && col < nb) {
-                a.Z[row + (int64_t)(k0 + col) * a.ldz] = z[i][j];
-                a.Up[row + (int64_t)col * L] = z[i][j] - ((row == k0 + col) ? 1.0 : 0.0);
-            }
-        }
-    for (int c = t; c < nb; c += NT) a.rsel[k0 + c] = k0 + c;
-    for (int row = t; row < L; row += NT) {
-        const bool piv = row >= k0 && row < k0 + nb;
-        if (k0 == 0)
-            a.used[row] = piv ? 1 : 0;
-        else if (piv)
-            a.used[row] = 1;
-    }
-    // pivot rows of the columns outside the panel: rows k0 .. k0 + nb - 1
+    // Panels of up to 256 rows load the pivot rows of the outside columns (Q)
+    // here, so that the loads complete during the elimination.
+    constexpr bool QPRE = !WHOLE && RB <= 2;
+    constexpr int QPT = QPRE ? (S::kRows - 64) / NW : 1;
     const int nout = L - nb;
-    for (int e = t; e < nb * nout; e += NT) {
-        const int c = e % nb, j = e / nb;
-        const int gj = j < k0 ? j : j + nb;
-        a.Q[c + (int64_t)gj * nb] = src[(k0 + c) + (int64_t)gj * lds];
+    double qv[QPT];
+    if constexpr (QPRE) {
+#pragma unroll
+        for (int q = 0; q < QPT; ++q) {
+            const int j = w + NW * q, gj = j < k0 ? j : j + nb;
+            qv[q] = (lane < nb && j < nout) ? src[(k0 + lane) + (int64_t)gj * lds] : 0.0;
+        }
     }
-    return true;
-}
+    bool viol = false;
+    if (!WHOLE && k0 > 0) {
+        // the rows before the panel must be the used ones and no other
+        for (int row = t; row < L; row += NT)
+            if ((a.used[row] != 0) != (row < k0)) viol = true;
+    }
 
-// The same elimination for panels of up to 256 rows with a flag per step
-// instead of a barrier per column block (k0 a multiple of 32 here, and the
-// pivot row k0 + c in slot 0 of lane k0 mod 64 + c).  LDS holds the multipliers of all
-// 64 steps (128 KB), so nothing is overwritten: the owner of step c
-// publishes its multipliers, pivot and inverse pivot and then raises the
-// step's flag, and every other wave applies step c as soon as it sees the
-// flag.  Waves run the steps in order, and a step only waits for steps of
-// lower-numbered waves, so every wait ends.  Issue priority goes by distance
-// to ownership (the owner of the running block, then the next two owners),
-// and the checks of block b are done by a wave that replays it anyway
-// (b + 4, else 0; for b = 0 and a panel of at most eight columns, wave 1,
-// which then only follows the steps).
-template <int RR>
-__device__ __attribute__((always_inline)) inline bool wpanel_pipe(const LeafArgs &a) {
-    constexpr int NW = 8, NT = 64 * NW, CW = 64 / NW;  // waves, threads, columns per wave
-    static_assert(RR <= 4, "the multipliers of 64 steps fill 128 KB of LDS at 256 rows");
-    __shared__ double fst[64][RR][64];  // multipliers of each step, by slot and lane
-    __shared__ double pst[2][64];       // inverse pivot and pivot of each step
-    __shared__ int rdy[64];             // step published
-    const int t = threadIdx.x, lane = t & 63;
-    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int L = a.L, k0 = a.k0, nb = a.nb;
-    const double *src = a.in ? static_cast<const double *>(a.in) : a.Z;
-    const int64_t lds = a.in ? a.ldi : a.ldz;
-    // slot 0 of lane o + c holds row k0 + c, o = k0 mod 64 (0, or 32 for
-    // 32-column panels)
-    const int rot = k0 >> 6, o = k0 & 63;
-    bool viol = o + nb > 64 || L > 64 * RR || nb < 1;
-    if (viol) return false;  // the same in every thread
-    if (t < 64) rdy[t] = 0;
-    int rowr[RR];
-    int rel[RR];  // row - k0 for rows inside the leaf (negative before k0), else -1
+    const int nblk = (nb + 15) >> 4, p0 = k0 >> 4;
+    double *const F = sm + S::oF, *const R = sm + S::oR;
+    double *const dr = sm + S::oDr, *const dm = sm + S::oDm, *const dump = sm + S::oDump;
+    constexpr auto kSteps = std::make_integer_sequence<int, 16>{};
+    d4_t D{0.0, 0.0, 0.0, 0.0};  // the diagonal block in the wave that runs its chain
+    // block column b of every row block and row block p0 + b to panel buffer u
+    auto publish = [&](const int b, const int u) {
+        const int ln = opaque(lane0), rr = ln & 15, g = ln >> 4;
+        double *pc = sm + S::oPc + u * 16 * S::kFLd, *pr = sm + S::oPr + u * 16 * S::kPrLd;
+        const int ow = (p0 + b) % NW, oi = (p0 + b) / NW;
+        static_for<NC>([&](auto c) {
+            if (c == b) {
 #pragma unroll
-    for (int i = 0; i < RR; ++i) {
-        rowr[i] = lane + 64 * ((i + rot) % RR);
-        rel[i] = (i + rot < RR && rowr[i] < L) ? lane + 64 * i - o : -1;
-    }
-    double z[RR][CW];
+                for (int i = 0; i < RB; ++i)
 #pragma unroll
-    for (int i = 0; i < RR; ++i)
+                    for (int v = 0; v < 4; ++v) pc[(4 * v + g) * S::kFLd + 16 * (w + NW * i) + rr] = acc[i][c][v];
+                branch_end<c>();
+            }
+        });
+        if (w == ow) {
+            static_for<RB>([&](auto i) {
+                if (i == oi) {
 #pragma unroll
-        for (int j = 0; j < CW; ++j) {
-            const int col = CW * w + j;
-            z[i][j] = (rowr[i] < L && col < nb) ? src[rowr[i] + (int64_t)(k0 + col) * lds] : 0.0;
+                    for (int c = 0; c < NC; ++c)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) pr[rr * S::kPrLd + 16 * c + 4 * v + g] = acc[i][c][v];
+                    branch_end<i>();
+                }
+            });
         }
-    const int nout = L - nb;
-    // pivot rows of the columns outside the panel (rows k0 .. k0 + nb - 1,
-    // gathered into Q once every check has passed), loaded now so that the
-    // loads complete during the elimination
-    constexpr int QPT = 4096 * (RR - 1) / NT;  // nb (L - nb) <= 64 (64 RR - 64)
-    double qv[QPT > 0 ? QPT : 1];
-#pragma unroll
-    for (int r = 0; r < QPT; ++r) {
-        const int e = t + NT * r, c = e % nb, j = e / nb;
-        const int gj = j < k0 ? j : j + nb;
-        qv[r] = e < nb * nout ? src[(k0 + c) + (int64_t)gj * lds] : 0.0;
-    }
-    if (w == 0 && k0 > 0) {
-#pragma unroll
-        for (int i = 0; i < RR; ++i)
-            if (rowr[i] < L && ((a.used[rowr[i]] != 0) != (rowr[i] < k0))) viol = true;
-    }
-    __syncthreads();  // the flags are cleared
-
-    // The pivot row of a step first takes the scaled row; its multiplier is
-    // 0, so the step's fused multiply-add turns it into fma(-0, rv, rv), the
-    // value gj2d_run gives it.
-    auto own_step = [&](const int j) {
-        const int c = CW * w + j, pc = o + c;  // step, pivot lane
-        const double piv = readlane_f64(z[0][j], pc);
-        const double pinv = 1.0 / piv;
-        const bool pl = lane == pc;
-        double rv[CW], f[RR];
-#pragma unroll
-        for (int jj = 0; jj < CW; ++jj) rv[jj] = (jj == j) ? pinv : readlane_f64(z[0][jj], pc) * pinv;
-#pragma unroll
-        for (int i = 0; i < RR; ++i) {
-            f[i] = (i == 0 && pl) ? 0.0 : z[i][j];
-            fst[c][i][lane] = f[i];
-        }
-        if (lane == 0) {
-            pst[0][c] = pinv;
-            pst[1][c] = piv;
-        }
-#pragma unroll
-        for (int i = 0; i < RR; ++i) z[i][j] = 0.0;  // the pivot column restarts from 0
-        if (pl) {
-#pragma unroll
-            for (int jj = 0; jj < CW; ++jj) z[0][jj] = rv[jj];
-        }
-#pragma unroll
-        for (int i = 0; i < RR; ++i)
-#pragma unroll
-            for (int jj = 0; jj < CW; ++jj) z[i][jj] = fma(-f[i], rv[jj], z[i][jj]);
-        // the flag last: its release orders it after the stores above
-        if (lane == 0) __hip_atomic_store(&rdy[c], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-    };
-    auto wait_step = [&](const int c) {
-        while (__hip_atomic_load(&rdy[c], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) == 0)
-            __builtin_amdgcn_s_sleep(1);
-    };
-    // The checks of step c: the pivot finite and nonzero, and no unused row
-    // (rel > c; the pivot row's published multiplier is 0) larger in
-    // magnitude or not finite.
-    auto check = [&](const int c, const double (&f)[RR]) {
-        const double apiv = fabs(pst[1][c]);
-        bool v = !(apiv > 0.0) | !(apiv <= DBL_MAX);
-#pragma unroll
-        for (int i = 0; i < RR; ++i) v |= (rel[i] > c) & !(fabs(f[i]) <= apiv);
-        viol |= v;
-    };
-    auto replay_step = [&](const int c, const bool chk) {
-        const double pinv = pst[0][c];
-        const bool pl = lane == o + c;
-        double rv[CW], f[RR];
-#pragma unroll
-        for (int i = 0; i < RR; ++i) f[i] = fst[c][i][lane];
-#pragma unroll
-        for (int jj = 0; jj < CW; ++jj) rv[jj] = readlane_f64(z[0][jj], o + c) * pinv;
-        if (pl) {
-#pragma unroll
-            for (int jj = 0; jj < CW; ++jj) z[0][jj] = rv[jj];
-        }
-#pragma unroll
-        for (int i = 0; i < RR; ++i)
-#pragma unroll
-            for (int jj = 0; jj < CW; ++jj) z[i][jj] = fma(-f[i], rv[jj], z[i][jj]);
-        if (chk) check(c, f);
-    };
-    auto check_step = [&](const int c) {
-        double f[RR];
-#pragma unroll
-        for (int i = 0; i < RR; ++i) f[i] = fst[c][i][lane];
-        check(c, f);
     };
 
-    const bool cols = CW * w < nb;
-    const int nblk = (nb + CW - 1) / CW;
+    publish(0, 0);
+    if (w == p0 % NW) {
+        static_for<RB>([&](auto i) {
+            if (i == p0 / NW) {
+                D = acc[i][0];
+                branch_end<i>();
+            }
+        });
+        diag_chain(D, lane, dm, dr, dump, kSteps);
+    }
+#pragma unroll 1
     for (int b = 0; b < nblk; ++b) {
-        // issue priority by distance to ownership: the owner first, then the
-        // waves whose blocks come next
-        if (w == b)
+        const int u = S::kTwo ? b & 1 : 0;
+        const int lane = opaque(lane0), rr = lane & 15, g = lane >> 4;
+        double *const pc = sm + S::oPc + u * 16 * S::kFLd, *const pr = sm + S::oPr + u * 16 * S::kPrLd;
+        __syncthreads();
+        // ---- panels ----
+        constexpr int RCH = (S::kRows + 63) / 64, CCH = (S::kCols + 63) / 64;
+#pragma unroll 1
+        for (int tk = w; tk < RCH + CCH; tk += NW) {
+            double x[16];
+            if (tk < RCH) {
+                const int row = 64 * tk + lane;
+                const bool chk = row >= k0 + 16 * (b + 1) && row < L;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) x[j] = pc[j * S::kFLd + row];
+                const bool bad = row_steps(x, dr + rr, dm[17 * rr], F + row, S::kFLd, kSteps);
+                viol = viol | (chk & bad);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) pc[j * S::kFLd + row] = x[j];
+            } else {
+                const int col = 64 * (tk - RCH) + lane;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) x[j] = pr[j * S::kPrLd + col];
+                col_steps(x, dm + rr, dr[17 * rr], R + col, S::kRLd, kSteps);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) pr[j * S::kPrLd + col] = x[j];
+            }
+        }
+        if (w == NW - 1) {
+            // the checks inside the diagonal block
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int e = lane + 64 * q, k = e >> 4, l = e & 15;
+                const double piv = dm[17 * k];
+                viol = viol | !plain_pivot(piv) | ((l > k) & !(fabs(dm[e]) <= fabs(piv)));
+            }
+        }
+        __syncthreads();
+        // ---- update ----
+        const int p = p0 + b, ow = p % NW, oi = p / NW;  // the pivot rows' owner
+        // the new values of the block column and, in their owner, of the pivot rows
+        static_for<NC>([&](auto c) {
+            if (c == b) {
+                static_for<RB>([&](auto i) {
+                    if (!(w == ow && i == oi)) {
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) acc[i][c][v] = pc[(4 * v + g) * S::kFLd + 16 * (w + NW * i) + rr];
+                        branch_end<NC * i + c>();
+                    }
+                });
+            }
+        });
+        if (w == ow) {
+            static_for<RB>([&](auto i) {
+                if (i == oi) {
+                    static_for<NC>([&](auto c) {
+                        if (c == b) {
+                            acc[i][c] = D;
+                            branch_end<NC * i + c>();
+                        } else {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) acc[i][c][v] = pr[rr * S::kPrLd + 16 * c + 4 * v + g];
+                            branch_end<NC * i + c>();
+                        }
+                    });
+                }
+            });
+        }
+        if constexpr (!S::kTwo) __syncthreads();
+        double fa[RB][4];
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) fa[i][q] = -F[(4 * q + g) * S::kFLd + 16 * (w + NW * i) + rr];
+        const bool more = b + 1 < nblk;
+        const int nw = (p + 1) % NW, ni = (p + 1) / NW;
+        if (more && w == nw) {
             __builtin_amdgcn_s_setprio(3);
-        else if (w == b + 1)
-            __builtin_amdgcn_s_setprio(2);
-        else if (w == b + 2)
-            __builtin_amdgcn_s_setprio(1);
-        // the checking wave of block b (see above)
-        int cw = (b + NW / 2) % NW;
-        if (CW * cw >= nb) cw = b == 0 ? 1 : 0;
-        const bool chk = w == cw;
-        if (w == b) {
+            // the next diagonal block first, and its chain
+            static_for<NC>([&](auto c) {
+                if (c == b + 1) {
+                    static_for<RB>([&](auto i) {
+                        if (i == ni) {
 #pragma unroll
-            for (int j = 0; j < CW; ++j)
-                if (CW * b + j < nb) own_step(j);
+                            for (int q = 0; q < 4; ++q)
+                                acc[i][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                                    R[(4 * q + g) * S::kRLd + 16 * c + rr], fa[i][q], acc[i][c], 0, 0, 0);
+                            D = acc[i][c];
+                            branch_end<NC * i + c>();
+                        }
+                    });
+                }
+            });
+            diag_chain(D, lane, dm, dr, dump, kSteps);
             __builtin_amdgcn_s_setprio(0);
-        } else if (cols) {
-            for (int c = CW * b; c < CW * b + CW && c < nb; ++c) {
-                wait_step(c);
-                replay_step(c, chk);
-            }
-        } else if (chk) {
-            for (int c = CW * b; c < CW * b + CW && c < nb; ++c) {
-                wait_step(c);
-                check_step(c);
-            }
         }
+        static_for<NC>([&](auto c) {
+            if (c != b && c < nblk) {
+                double fb[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) fb[q] = R[(4 * q + g) * S::kRLd + 16 * c + rr];
+                static_for<RB>([&](auto i) {
+                    if (!(w == ow && i == oi) && !(more && c == b + 1 && w == nw && i == ni)) {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            acc[i][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[q], fa[i][q], acc[i][c], 0, 0, 0);
+                        branch_end<NC * i + c>();
+                    }
+                });
+            }
+        });
+        if (more) publish(b + 1, S::kTwo ? (b + 1) & 1 : 0);
     }
-    // Outputs the search rewrites in full if a check failed, and that it does
-    // not read, are stored before the vote: U' always, the panel's columns of
-    // Z when the panel is read from the leaf's input.
-    const bool zout = a.in != nullptr;
-#pragma unroll
-    for (int i = 0; i < RR; ++i)
-#pragma unroll
-        for (int j = 0; j < CW; ++j) {
-            const int row = rowr[i], col = CW * w + j;
-            if (row < L && col < nb) {
-                a.Up[row + (int64_t)col * L] = z[i][j] - ((row == k0 + col) ? 1.0 : 0.0);
-                if (zout) a.Z[row + (int64_t)(k0 + col) * a.ldz] = z[i][j];
-            }
-        }
     if (__syncthreads_or(viol)) return false;
 
-    if (!zout) {
+    const int ln = opaque(lane0), sr = ln & 15, sg = ln >> 4;
 #pragma unroll
-        for (int i = 0; i < RR; ++i)
+    for (int i = 0; i < RB; ++i)
 #pragma unroll
-            for (int j = 0; j < CW; ++j) {
-                const int row = rowr[i], col = CW * w + j;
-                if (row < L && col < nb) a.Z[row + (int64_t)(k0 + col) * a.ldz] = z[i][j];
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = 16 * (w + NW * i) + sr, col = 16 * c + 4 * v + sg;
+                if (row < L && col < nb) {
+                    const double x = acc[i][c][v];
+                    if (WHOLE) {
+                        static_cast<TO *>(a.out)[row + (int64_t)col * a.ldo] = (TO)x;
+                    } else {
+                        a.Z[row + (int64_t)(k0 + col) * a.ldz] = x;
+                        a.Up[row + (int64_t)col * L] = x - ((row == k0 + col) ? 1.0 : 0.0);
+                    }
+                }
             }
-    }
-    for (int c = t; c < nb; c += NT) a.rsel[k0 + c] = k0 + c;
-    for (int row = t; row < L; row += NT) {
-        const bool piv = row >= k0 && row < k0 + nb;
-        if (k0 == 0)
-            a.used[row] = piv ? 1 : 0;
-        else if (piv)
-            a.used[row] = 1;
-    }
+    if constexpr (!WHOLE) {
+        for (int c = t; c < nb; c += NT) a.rsel[k0 + c] = k0 + c;
+        for (int row = t; row < L; row += NT) {
+            const bool piv = row >= k0 && row < k0 + nb;
+            if (k0 == 0)
+                a.used[row] = piv ? 1 : 0;
+            else if (piv)
+                a.used[row] = 1;
+        }
+        if constexpr (QPRE) {
 #pragma unroll
-    for (int r = 0; r < QPT; ++r) {
-        const int e = t + NT * r, c = e % nb, j = e / nb;
-        const int gj = j < k0 ? j : j + nb;
-        if (e < nb * nout) a.Q[c + (int64_t)gj * nb] = qv[r];
+            for (int q = 0; q < QPT; ++q) {
+                const int j = w + NW * q, gj = j < k0 ? j : j + nb;
+                if (lane < nb && j < nout) a.Q[lane + (int64_t)gj * nb] = qv[q];
+            }
+        } else {
+#pragma unroll 8
+            for (int j = w; j < nout; j += NW) {
+                const int gj = j < k0 ? j : j + nb;
+                if (lane < nb) a.Q[lane + (int64_t)gj * nb] = src[(k0 + lane) + (int64_t)gj * lds];
+            }
+        }
     }
     return true;
 }
 
 // ------------------------------------------------- two-workgroup panel ---
-// The pipelined elimination of a full 64-column panel of at most 256 rows on
+// The speculative elimination of a full 64-column panel of 129 to 256 rows on
 // two workgroups (two CUs), each holding 32 of its columns (eight waves of
-// four), so that each CU replays half of the steps' updates.  Workgroup h
-// owns steps 32h .. 32h + 31 and runs them as wpanel_pipe does (LDS flags);
-// the wave that owned the previous column block, which is then caught up and
+// four columns for all rows: lane l, slot i of a wave holds row l + 64 ((i +
+// k0 / 64) mod RR), so the pivot row of step c is slot 0 of lane c).
+// Workgroup h owns steps 32h .. 32h + 31: the wave that holds the column runs
+// the step alone (pivot row by readlane), publishes its multipliers, pivot
+// and inverse pivot to LDS and raises the step's flag, and every other wave
+// applies the step when it sees the flag; issue priority goes by distance to
+// ownership.  The wave that owned the previous column block, which is then caught up and
 // far from its next turn, stores each step's multipliers and inverse pivot
 // to the panel's exchange area in device memory, and the other workgroup
 // replays the step from there.
@@ -1238,7 +1204,8 @@ __global__ void __launch_bounds__(512) leaf_duo(LeafArgs a) {
     } else if (blockIdx.x != 0) {
         return;
     }
-    gj2d_run<32, 8, 4, false, double, double>(a);
+    __shared__ __attribute__((aligned(16))) double sm[RunLds<32, 8, 4>::kDoubles];
+    gj2d_run<32, 8, 4, false, double, double>(a, sm);
 }
 
 // Fills the exchange areas of a leaf's two-workgroup panels: every value
@@ -1251,21 +1218,16 @@ __global__ void __launch_bounds__(256) leaf_duo_reset(double *xg, int64_t nd, in
 
 template <int TR, int RR, int RC, bool WHOLE, typename TI, typename TO>
 __device__ __attribute__((always_inline)) inline void gj2d_any(const LeafArgs &a) {
+    constexpr int NW = TR / 4;                 // waves
+    constexpr int RB = TR * RR / (16 * NW);    // 16-row blocks per wave
+    static_assert(RB * 16 * NW == TR * RR && NW * 64 == 16 * TR, "row blocks cover the rows");
+    constexpr int D0 = BlkLds<NW, RB, RC>::kDoubles, D1 = RunLds<TR, RR, RC>::kDoubles;
+    __shared__ __attribute__((aligned(16))) double sm[D0 > D1 ? D0 : D1];
     if (a.spec && *a.spec != 0) {
-        bool ok;
-        if constexpr (WHOLE) {
-            ok = gj2d_spec<TR, RR, RC, TI, TO>(a);
-        } else {
-            static_assert(TR * RR % 64 == 0, "whole waves hold the panel's rows");
-            if constexpr (TR == 32 && TR * RR <= 256)
-                ok = wpanel_pipe<TR * RR / 64>(a);
-            else
-                ok = wpanel_spec<TR * RR / 64, TR / 4>(a);
-        }
-        if (ok) return;
+        if (gj_blocked<NW, RB, RC, WHOLE, TI, TO>(a, sm)) return;
         if (threadIdx.x == 0) *a.spec = 0;
     }
-    gj2d_run<TR, RR, RC, WHOLE, TI, TO>(a);
+    gj2d_run<TR, RR, RC, WHOLE, TI, TO>(a, sm);
 }
 
 template <int TR, int RR, int RC, bool WHOLE, typename TI, typename TO>
