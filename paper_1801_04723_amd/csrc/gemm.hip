@@ -105,6 +105,26 @@ __device__ inline void tile_coords(int t, int tstart, int tiles_m, int tiles_n, 
     }
 }
 
+// Tile order and k range of a product with triangular operands (tri flags):
+// the tiles with the longest k range come first in the grid, so that the last
+// wave of workgroups is short, and the range (whole BK slabs, kend at most K
+// rounded up) leaves out the slabs in which the tile's rows of A or columns of
+// B are all zero.  What is left out are products with zero: the sums are the
+// same.
+__device__ inline void tri_tiles(int tri, int tiles_m, int tiles_n, int &tm, int &tn) {
+    if (tri & kTriALower) tm = tiles_m - 1 - tm;
+    if (tri & kTriBUpper) tn = tiles_n - 1 - tn;
+}
+__device__ inline void tri_range(int tri, int m0, int bm, int n0, int bn, int bk, int K, int &kt0, int &kt1) {
+    int lo = 0, hi = K;
+    if (tri & kTriALower) hi = min(hi, m0 + bm);
+    if (tri & kTriBUpper) hi = min(hi, n0 + bn);
+    if (tri & kTriAUpper) lo = max(lo, m0);
+    if (tri & kTriBLower) lo = max(lo, n0);
+    kt0 = lo / bk;
+    kt1 = max(kt0, (hi + bk - 1) / bk);
+}
+
 template <int BM, int BN, int BK, int WM, int WN, typename T, int NG>
 __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
     constexpr int NT = 256;
@@ -128,6 +148,8 @@ __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
     int tm, tn;
     tile_coords(bid - tstart, tstart, tiles_m, (P.n + BN - 1) / BN, P.lower != 0, tm, tn);
 
+    const int tri = P.tri;
+    if (tri) tri_tiles(tri, tiles_m, (P.n + BN - 1) / BN, tm, tn);
     const int M = P.m, N = P.n, K = P.k;
     const int m0 = tm * BM, n0 = tn * BN;
     const T *__restrict__ A = static_cast<const T *>(P.A);
@@ -185,14 +207,15 @@ __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = acc_t{0, 0, 0, 0};
 
-    const int KT = (K + BK - 1) / BK;
-    if (KT > 0) {
-        gload(0);
-        sstore(0);
+    int kt0 = 0, KT = (K + BK - 1) / BK;
+    if (tri) tri_range(tri, m0, BM, n0, BN, BK, K, kt0, KT);
+    if (KT > kt0) {
+        gload(kt0 * BK);
+        sstore(kt0 & 1);
     }
     __syncthreads();
     const int krow = lane >> 4, kcol = lane & 15;
-    for (int kt = 0; kt < KT; ++kt) {
+    for (int kt = kt0; kt < KT; ++kt) {
         const int cur = kt & 1;
         if (kt + 1 < KT) gload((kt + 1) * BK);
 #pragma unroll
@@ -283,6 +306,8 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     const int tstart = g.tile_start[pi], tiles_m = g.tiles_m[pi];
     int tm, tn;
     tile_coords(bid - tstart, tstart, tiles_m, (P.n + BN - 1) / BN, P.lower != 0, tm, tn);
+    const int tri = P.tri;
+    if (tri) tri_tiles(tri, tiles_m, (P.n + BN - 1) / BN, tm, tn);
     const int M = P.m, N = P.n, K = P.k;
     const int m0 = tm * BM, n0 = tn * BN;
     const int64_t lda = P.lda, ldb = P.ldb;
@@ -365,7 +390,16 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
         }
     };
 
-    const int KT = K / BK;
+    int KT = K / BK;
+    if (tri) {
+        int kt0;
+        tri_range(tri, m0, BM, n0, BN, BK, K, kt0, KT);
+#pragma unroll
+        for (int i = 0; i < AV; ++i) pa[i] += kt0 * astep;
+#pragma unroll
+        for (int i = 0; i < BV; ++i) pb[i] += kt0 * BK;
+        KT -= kt0;
+    }
     if (KT > 0) {
         gload();
         sstore(0);

@@ -180,6 +180,8 @@ void plan_node_spd(Plan &P, Ref in, Ref out, int64_t m, int64_t wsoff, int level
 //   S = A22 - L21 U12;  {T1 = L21 Li11, T2 = Ui11 U12};  (Li22, Ui22) = rec(S);
 //   {Li21 = -Li22 T1, Ui12 = -T2 Ui22},
 // and X = Ui Li closes the schedule.  Leaves factor and invert in one kernel.
+// Every product but S has a triangular operand, whose zero triangle its tiles
+// skip: about 2 n^3 operations instead of 4.3 n^3.
 void plan_node_lu(Plan &P, Ref in, Ref li, Ref ui, int64_t m, int64_t wsoff, int level,
                   int64_t col0) {
     if (m <= P.leaf) {
@@ -209,16 +211,16 @@ void plan_node_lu(Plan &P, Ref in, Ref li, Ref ui, int64_t m, int64_t wsoff, int
     const int64_t next = wsoff + 4 * n1 * n2 + n2 * n2;
     P.ws_elems = std::max(P.ws_elems, next);
     const Ref none{BUF_WS, 0, 1};
-    const PGemm g_u12{Li11, A12, none, U12, n1, n2, n1, 1.0, 0.0, 0};
-    const PGemm g_l21{A21, Ui11, none, L21, n2, n1, n1, 1.0, 0.0, 0};
+    const PGemm g_u12{Li11, A12, none, U12, n1, n2, n1, 1.0, 0.0, 0, 0, kTriALower};
+    const PGemm g_l21{A21, Ui11, none, L21, n2, n1, n1, 1.0, 0.0, 0, 0, kTriBUpper};
     push_products(P, level, g_u12, &g_l21);
     push_products(P, level, PGemm{L21, U12, A22, S, n2, n2, n1, -1.0, 1.0, 0}, nullptr);
-    const PGemm g_t1{L21, Li11, none, T1, n2, n1, n1, 1.0, 0.0, 0};
-    const PGemm g_t2{Ui11, U12, none, T2, n1, n2, n1, 1.0, 0.0, 0};
+    const PGemm g_t1{L21, Li11, none, T1, n2, n1, n1, 1.0, 0.0, 0, 0, kTriBLower};
+    const PGemm g_t2{Ui11, U12, none, T2, n1, n2, n1, 1.0, 0.0, 0, 0, kTriAUpper};
     push_products(P, level, g_t1, &g_t2);
     plan_node_lu(P, S, Li22, Ui22, n2, next, level + 1, col0 + n1);
-    const PGemm g_li21{Li22, T1, none, Li21, n2, n1, n2, -1.0, 0.0, 0};
-    const PGemm g_ui12{T2, Ui22, none, Ui12, n1, n2, n2, -1.0, 0.0, 0};
+    const PGemm g_li21{Li22, T1, none, Li21, n2, n1, n2, -1.0, 0.0, 0, 0, kTriALower};
+    const PGemm g_ui12{T2, Ui22, none, Ui12, n1, n2, n2, -1.0, 0.0, 0, 0, kTriBUpper};
     push_products(P, level, g_li21, &g_ui12);
 }
 
@@ -243,7 +245,8 @@ Plan make_plan_lu(int64_t n, int64_t lda, int64_t ldx, int64_t leaf) {
     }
     plan_node_lu(P, Ref{BUF_A, 0, lda}, LI, UI, n, 2 * n * n, 0, 0);
     const Ref none{BUF_WS, 0, 1};
-    push_products(P, 0, PGemm{UI, LI, none, Ref{BUF_X, 0, ldx}, n, n, n, 1.0, 0.0, 0}, nullptr);
+    push_products(P, 0, PGemm{UI, LI, none, Ref{BUF_X, 0, ldx}, n, n, n, 1.0, 0.0, 0, 0, kTriAUpper | kTriBLower},
+                  nullptr);
     return P;
 }
 
@@ -311,7 +314,7 @@ GemmProb make_prob(char *const base[3], size_t es, const PGemm &g) {
                     at(g.d),          g.a.ld,        g.b.ld,
                     use_c ? g.c.ld : 1, g.d.ld,      (int32_t)g.m,
                     (int32_t)g.n,     (int32_t)g.k,  g.add_identity,
-                    g.alpha,          g.beta,        g.lower};
+                    g.alpha,          g.beta,        (int16_t)g.lower, (int16_t)g.tri};
 }
 
 namespace {

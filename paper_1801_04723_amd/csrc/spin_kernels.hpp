@@ -31,6 +31,8 @@ constexpr int kLeafMaxOrder = 2048;
 // (the result transposed, n x m); for a lower problem only the elements below
 // the diagonal are, so DT == D, lddt == ldd is the mirror.  DT must not
 // overlap A, B or C0 (except where DT == D == C0 in the mirror form).
+// tri: operands that are zero in one triangle, so that a tile skips the k
+// range where its rows of A or its columns of B hold only those zeros.
 // 112 bytes: a group of kMaxBatch products stays within the 4 KiB of kernel
 // arguments.
 struct GemmProb {
@@ -42,11 +44,16 @@ struct GemmProb {
     int32_t m, n, k;
     int32_t add_identity;
     double alpha, beta;
-    int32_t lower;
+    int16_t lower;
+    int16_t tri;  // kTri* flags
     int32_t lddt;
     void *DT;
 };
 static_assert(sizeof(GemmProb) == 112, "GemmProb layout");
+constexpr int kTriALower = 1;  // A[i][k] = 0 for k > i
+constexpr int kTriAUpper = 2;  // A[i][k] = 0 for k < i
+constexpr int kTriBLower = 4;  // B[k][j] = 0 for k < j
+constexpr int kTriBUpper = 8;  // B[k][j] = 0 for k > j
 
 // One gemm_launch() call takes up to kMaxBatch independent products; products
 // that share a kernel configuration run in one grid (every workgroup finds

@@ -23,13 +23,15 @@ struct Ref {
 };
 
 // One block product of the schedule: D = alpha A B + beta C (+ I).  With
-// lower set (m == n) only the tiles on or below the diagonal are computed.
+// lower set (m == n) only the tiles on or below the diagonal are computed;
+// tri (kTri* flags) marks operands that are zero in one triangle.
 struct PGemm {
     Ref a, b, c, d;
     int64_t m, n, k;
     double alpha, beta;
     int add_identity;
     int lower;
+    int tri;
 };
 
 // One step: a group of independent products (kind 0), a leaf (kind 1), a
