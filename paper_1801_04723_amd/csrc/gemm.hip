@@ -23,6 +23,8 @@
 //   v_mfma_f32_16x16x4f32 : lane l, element v  ->  D^T row 4*(l/16) + v
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "spin_kernels.hpp"
 
 namespace spin {
@@ -262,13 +264,19 @@ __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
     }
 }
 
-// Fast path.  Requires 16-byte aligned operands, leading dimensions that are
-// multiples of the vector width, M a multiple of the vector width and K a
+// Fast path.  The main loop has no control flow: the edge rows/columns of a
+// tile are clamped once (what they load only reaches outputs the epilogue
+// discards), each thread keeps one pointer per 16-byte global load and advances
+// it by one slab per step.  RAG = false requires 16-byte aligned operands,
+// leading dimensions and M that are multiples of the vector width and K a
 // multiple of BK -- true for every block product of the recursion when the
-// order is a multiple of 64.  The main loop then has no control flow: the
-// edge rows/columns of a tile are clamped once (what they load only reaches
-// outputs the epilogue discards), each thread keeps one pointer per 16-byte
-// global load and advances it by one slab per step.
+// order is a multiple of 64.  RAG = true takes any operands with M at least
+// the vector width: 16-byte loads at element alignment, a vector that reaches
+// beyond row M - 1 loaded from row M - VW on and stored to LDS at those rows
+// (its neighbours' entries, with the same values), and the last K mod BK
+// columns as one more slab, loaded element by element with zeros beyond K.
+// m = 1537, n = 1001, k = 777 in FP64: 113 us in the guarded kernel above,
+// which loads single elements, 64 us here.
 //
 // The K slab is split into four contiguous chunks of KQ = BK/4 values, one per
 // lane group q = lane/16, and MFMA step kk consumes k = q*KQ + kk in group q
@@ -280,11 +288,13 @@ __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
 // 32 x 32 tile.  Eight waves put four on each SIMD (two when a product
 // leaves one workgroup per CU), so more of the slab loads and barriers hide
 // behind other waves' matrix instructions.
-template <int BM, int BN, int BK, int WM, int WN, typename T, int NG, int NW>
+template <int BM, int BN, int BK, int WM, int WN, typename T, int NG, int NW, bool RAG>
 __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     constexpr int NT = 64 * NW;
     constexpr int VW = 16 / sizeof(T);
     typedef T vec_t __attribute__((ext_vector_type(VW)));
+    typedef T uvec_t __attribute__((ext_vector_type(VW), aligned(sizeof(T))));
+    using ld_t = std::conditional_t<RAG, uvec_t, vec_t>;  // global loads and A's LDS stores
     constexpr int WAVES_M = BM / WM;
     static_assert(WAVES_M * (BN / WN) == NW, "NW waves per workgroup");
     constexpr int TM = WM / 16, TN = WN / 16;
@@ -297,7 +307,9 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     static_assert(AV * VW * NT == BM * BK && BV * VW * NT == BN * BK, "tile/thread mismatch");
     using acc_t = typename Mma<T>::acc_t;
 
-    __shared__ __attribute__((aligned(16))) T As[2][BK * A_LD];
+    // a ragged tile with fewer than VW rows stores up to VW - 1 entries before
+    // a slab row, into the padding of the row before it
+    __shared__ __attribute__((aligned(16))) T As[2][BK * A_LD + (RAG ? VW : 0)];
     __shared__ __attribute__((aligned(16))) T Bs[2][BN * B_LD];
 
     const int bid = blockIdx.x;
@@ -319,9 +331,9 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
 #pragma unroll
     for (int i = 0; i < AV; ++i) {
         const int v = tid + NT * i, r = (v % (BM / VW)) * VW, c = v / (BM / VW);
-        const int row = m0 + r < M ? m0 + r : M - VW;
+        const int row = RAG ? min(m0 + r, M - VW) : m0 + r < M ? m0 + r : M - VW;
         pa[i] = static_cast<const T *>(P.A) + row + (int64_t)c * lda;
-        sa[i] = c * A_LD + r;
+        sa[i] = RAG ? VW + c * A_LD + row - m0 : c * A_LD + r;
     }
     const T *pb[BV];
     int sb[BV];
@@ -342,18 +354,34 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     auto gload = [&]() {
 #pragma unroll
         for (int i = 0; i < AV; ++i) {
-            ra[i] = *reinterpret_cast<const vec_t *>(pa[i]);
+            ra[i] = *reinterpret_cast<const ld_t *>(pa[i]);
             pa[i] += astep;
         }
 #pragma unroll
         for (int i = 0; i < BV; ++i) {
-            rb[i] = *reinterpret_cast<const vec_t *>(pb[i]);
+            rb[i] = *reinterpret_cast<const ld_t *>(pb[i]);
             pb[i] += BK;
+        }
+    };
+    // the last KR = K mod BK columns of A and rows of B, zeros beyond
+    const int KR = RAG ? K % BK : 0;
+    auto gload_tail = [&]() {
+#pragma unroll
+        for (int i = 0; i < AV; ++i) {
+            const int c = (tid + NT * i) / (BM / VW);
+#pragma unroll
+            for (int e = 0; e < VW; ++e) ra[i][e] = c < KR ? pa[i][e] : T(0);
+        }
+#pragma unroll
+        for (int i = 0; i < BV; ++i) {
+            const int kb = ((tid + NT * i) % (BK / VW)) * VW;
+#pragma unroll
+            for (int e = 0; e < VW; ++e) rb[i][e] = kb + e < KR ? pb[i][e] : T(0);
         }
     };
     auto sstore = [&](int buf) {
 #pragma unroll
-        for (int i = 0; i < AV; ++i) *reinterpret_cast<vec_t *>(&As[buf][sa[i]]) = ra[i];
+        for (int i = 0; i < AV; ++i) *reinterpret_cast<ld_t *>(&As[buf][sa[i]]) = ra[i];
 #pragma unroll
         for (int i = 0; i < BV; ++i) *reinterpret_cast<vec_t *>(&Bs[buf][sb[i]]) = rb[i];
     };
@@ -368,7 +396,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     // B fragments are fetched one 16-byte vector (VW consecutive k) per
     // column block at a time, which bounds their registers to TN vectors.
     auto compute = [&](int buf) {
-        const T *as = &As[buf][(q * KQ) * A_LD + wm0 + c16];
+        const T *as = &As[buf][(RAG ? VW : 0) + (q * KQ) * A_LD + wm0 + c16];
         const T *bs = &Bs[buf][(wn0 + c16) * B_LD + q * KQ];
 #pragma unroll
         for (int kc = 0; kc < KQ / VW; ++kc) {
@@ -390,17 +418,36 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
         }
     };
 
-    int KT = K / BK;
+    int KT = K / BK, kend = KT;
     if (tri) {
         int kt0;
-        tri_range(tri, m0, BM, n0, BN, BK, K, kt0, KT);
+        tri_range(tri, m0, BM, n0, BN, BK, K, kt0, kend);
+        KT = max(kt0, min(KT, kend));
 #pragma unroll
         for (int i = 0; i < AV; ++i) pa[i] += kt0 * astep;
 #pragma unroll
         for (int i = 0; i < BV; ++i) pb[i] += kt0 * BK;
         KT -= kt0;
     }
-    if (KT > 0) {
+    if constexpr (RAG) {
+        // a triangular k range that ends before K has no tail slab
+        const int KS = KT + (KR > 0 && (!tri || kend > K / BK));
+        auto next = [&](int kt) {
+            if (kt < KT)
+                gload();
+            else if (kt < KS)
+                gload_tail();
+        };
+        next(0);
+        sstore(0);
+        __syncthreads();
+        for (int kt = 0; kt < KS; ++kt) {
+            next(kt + 1);
+            compute(kt & 1);
+            sstore((kt & 1) ^ 1);
+            __syncthreads();
+        }
+    } else if (KT > 0) {
         gload();
         sstore(0);
         __syncthreads();
@@ -834,15 +881,21 @@ int make_group(const GemmProb *probs, int count, GroupArgs<N> &g) {
 }
 
 // One launch of up to N products that share a kernel configuration.
-template <bool FAST, int BM, int BN, int BK, int WM, int WN, typename T, int N, int NW = 4>
-hipError_t launch_group(const GemmProb *probs, int count, hipStream_t s) {
+template <int BM, int BN, int BK, int WM, int WN, typename T, int N, int NW, bool RAG>
+hipError_t launch_fast(const GemmProb *probs, int count, hipStream_t s) {
     GroupArgs<N> g;
     const int total = make_group<BM, BN, N>(probs, count, g);
     if (total == 0) return hipSuccess;
-    if constexpr (FAST)
-        hipLaunchKernelGGL((gemm_fast<BM, BN, BK, WM, WN, T, N, NW>), dim3(total), dim3(64 * NW), 0, s, g);
-    else
-        hipLaunchKernelGGL((gemm_kernel<BM, BN, BK, WM, WN, T, N>), dim3(total), dim3(256), 0, s, g);
+    hipLaunchKernelGGL((gemm_fast<BM, BN, BK, WM, WN, T, N, NW, RAG>), dim3(total), dim3(64 * NW), 0, s, g);
+    return hipGetLastError();
+}
+
+template <typename T, int N>
+hipError_t launch_edge(const GemmProb *probs, int count, hipStream_t s) {
+    GroupArgs<N> g;
+    const int total = make_group<32, 32, N>(probs, count, g);
+    if (total == 0) return hipSuccess;
+    hipLaunchKernelGGL((gemm_kernel<32, 32, 32, 16, 16, T, N>), dim3(total), dim3(256), 0, s, g);
     return hipGetLastError();
 }
 
@@ -872,10 +925,11 @@ constexpr int fast_bk(int tile, int es) { return (tile == 128 && es == 8) ? kFas
 // Kernel configuration of one product, a function of that product alone (its
 // shape, leading dimensions and alignment), so that a product is computed
 // bit for bit the same whether it is launched alone or grouped with others.
+enum Path { kEdge = 0, kFast = 1, kRagged = 2 };
 struct Cfg {
     int tile;   // 128, 64 or 32; 256 for the eight-wave BF16 tiles
-    bool fast;  // branch-free vector path
-    bool operator==(const Cfg &o) const { return tile == o.tile && fast == o.fast; }
+    Path path;  // guarded, branch-free vector, vector with ragged edges
+    bool operator==(const Cfg &o) const { return tile == o.tile && path == o.path; }
 };
 
 Cfg choose_cfg(const GemmProb &p, DType dt) {
@@ -896,30 +950,37 @@ Cfg choose_cfg(const GemmProb &p, DType dt) {
         ((reinterpret_cast<uintptr_t>(p.A) | reinterpret_cast<uintptr_t>(p.B)) & 15) == 0;
     if (dt == kBF16 || dt == kBF16X3) {
         // float4 loads along m (A) and along k (B)
-        c.fast = p.m % 4 == 0 && p.k % 4 == 0 && p.lda % 4 == 0 && p.ldb % 4 == 0 && aligned;
+        c.path = p.m % 4 == 0 && p.k % 4 == 0 && p.lda % 4 == 0 && p.ldb % 4 == 0 && aligned ? kFast : kEdge;
         // plain BF16: eight-wave 256 x 256 tiles once they alone fill the
         // GPU; not for the lower-triangle mode
         const int64_t big = ((p.m + 255) / 256) * ((p.n + 255) / 256);
-        if (dt == kBF16 && c.fast && !p.lower && big >= 256) c.tile = 256;
+        if (dt == kBF16 && c.path == kFast && !p.lower && big >= 256) c.tile = 256;
         return c;
     }
     const int bk = fast_bk(c.tile, es);
-    c.fast = p.k > 0 && p.k % bk == 0 && p.m % vw == 0 && p.lda % vw == 0 && p.ldb % vw == 0 &&
-             aligned;
+    if (p.k <= 0 || p.m < vw) {
+        // no vector of A to load (an empty reduction, one to three rows)
+        c.path = kEdge;
+        c.tile = 32;
+    } else {
+        c.path = p.k % bk == 0 && p.m % vw == 0 && p.lda % vw == 0 && p.ldb % vw == 0 && aligned ? kFast : kRagged;
+    }
     return c;
+}
+
+template <typename T, int N, bool RAG>
+hipError_t launch_tile(int tile, const GemmProb *probs, int count, hipStream_t s) {
+    constexpr int ES = sizeof(T);
+    if (tile == 128) return launch_fast<128, 128, fast_bk(128, ES), 64, 32, T, N, 8, RAG>(probs, count, s);
+    if (tile == 64) return launch_fast<64, 64, fast_bk(64, ES), 32, 16, T, N, 8, RAG>(probs, count, s);
+    return launch_fast<32, 32, fast_bk(32, ES), 16, 16, T, N, 4, RAG>(probs, count, s);
 }
 
 template <typename T, int N>
 hipError_t launch_cfg(Cfg c, const GemmProb *probs, int count, hipStream_t s) {
-    constexpr int ES = sizeof(T);
-    if (c.tile == 128)
-        return c.fast ? launch_group<true, 128, 128, fast_bk(128, ES), 64, 32, T, N, 8>(probs, count, s)
-                      : launch_group<false, 128, 128, 16, 64, 64, T, N>(probs, count, s);
-    if (c.tile == 64)
-        return c.fast ? launch_group<true, 64, 64, fast_bk(64, ES), 32, 16, T, N, 8>(probs, count, s)
-                      : launch_group<false, 64, 64, 16, 32, 32, T, N>(probs, count, s);
-    return c.fast ? launch_group<true, 32, 32, fast_bk(32, ES), 16, 16, T, N>(probs, count, s)
-                  : launch_group<false, 32, 32, 32, 16, 16, T, N>(probs, count, s);
+    if (c.path == kEdge) return launch_edge<T, N>(probs, count, s);
+    return c.path == kFast ? launch_tile<T, N, false>(c.tile, probs, count, s)
+                           : launch_tile<T, N, true>(c.tile, probs, count, s);
 }
 
 template <bool X3, int N>
@@ -927,30 +988,32 @@ hipError_t launch_cfg_bf16(Cfg c, const GemmProb *probs, int count, hipStream_t 
     if constexpr (!X3)
         if (c.tile == 256) return launch_bf16_big_group<256, 256, 128, 64, N>(probs, count, s);
     if (c.tile == 128)
-        return c.fast ? launch_bf16_group<128, 128, 64, 32, X3, true, N, 8>(probs, count, s)
+        return c.path == kFast ? launch_bf16_group<128, 128, 64, 32, X3, true, N, 8>(probs, count, s)
                       : launch_bf16_group<128, 128, 64, 64, X3, false, N>(probs, count, s);
     if (c.tile == 64)
-        return c.fast ? launch_bf16_group<64, 64, 32, 32, X3, true, N>(probs, count, s)
+        return c.path == kFast ? launch_bf16_group<64, 64, 32, 32, X3, true, N>(probs, count, s)
                       : launch_bf16_group<64, 64, 32, 32, X3, false, N>(probs, count, s);
-    return c.fast ? launch_bf16_group<32, 32, 16, 16, X3, true, N>(probs, count, s)
+    return c.path == kFast ? launch_bf16_group<32, 32, 16, 16, X3, true, N>(probs, count, s)
                   : launch_bf16_group<32, 32, 16, 16, X3, false, N>(probs, count, s);
 }
 
 const char *cfg_name(Cfg c, DType dt) {
-    static const char *names[4][3][2] = {
-        {{"gemm_f64_128x128_edge", "gemm_f64_128x128"}, {"gemm_f64_64x64_edge", "gemm_f64_64x64"},
-         {"gemm_f64_32x32_edge", "gemm_f64_32x32"}},
-        {{"gemm_f32_128x128_edge", "gemm_f32_128x128"}, {"gemm_f32_64x64_edge", "gemm_f32_64x64"},
-         {"gemm_f32_32x32_edge", "gemm_f32_32x32"}},
-        {{"gemm_bf16_128x128_edge", "gemm_bf16_128x128"},
-         {"gemm_bf16_64x64_edge", "gemm_bf16_64x64"},
-         {"gemm_bf16_32x32_edge", "gemm_bf16_32x32"}},
-        {{"gemm_bf16x3_128x128_edge", "gemm_bf16x3_128x128"},
-         {"gemm_bf16x3_64x64_edge", "gemm_bf16x3_64x64"},
-         {"gemm_bf16x3_32x32_edge", "gemm_bf16x3_32x32"}}};
+    static const char *names[4][3][3] = {
+        {{"gemm_f64_128x128_edge", "gemm_f64_128x128", "gemm_f64_128x128_ragged"},
+         {"gemm_f64_64x64_edge", "gemm_f64_64x64", "gemm_f64_64x64_ragged"},
+         {"gemm_f64_32x32_edge", "gemm_f64_32x32", "gemm_f64_32x32_ragged"}},
+        {{"gemm_f32_128x128_edge", "gemm_f32_128x128", "gemm_f32_128x128_ragged"},
+         {"gemm_f32_64x64_edge", "gemm_f32_64x64", "gemm_f32_64x64_ragged"},
+         {"gemm_f32_32x32_edge", "gemm_f32_32x32", "gemm_f32_32x32_ragged"}},
+        {{"gemm_bf16_128x128_edge", "gemm_bf16_128x128", ""},
+         {"gemm_bf16_64x64_edge", "gemm_bf16_64x64", ""},
+         {"gemm_bf16_32x32_edge", "gemm_bf16_32x32", ""}},
+        {{"gemm_bf16x3_128x128_edge", "gemm_bf16x3_128x128", ""},
+         {"gemm_bf16x3_64x64_edge", "gemm_bf16x3_64x64", ""},
+         {"gemm_bf16x3_32x32_edge", "gemm_bf16x3_32x32", ""}}};
     if (c.tile == 256) return "gemm_bf16_256x256";
     const int ti = c.tile == 128 ? 0 : c.tile == 64 ? 1 : 2;
-    return names[(int)dt][ti][c.fast ? 1 : 0];
+    return names[(int)dt][ti][(int)c.path];
 }
 
 }  // namespace
