@@ -2,6 +2,7 @@
 // copies, transposes and deterministic Frobenius-norm reductions.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <climits>
 
 #include "spin_kernels.hpp"
@@ -9,26 +10,59 @@
 namespace spin {
 namespace {
 
-constexpr int kNormBlocks = 1024;
+constexpr int kNormBlocks = 256;
 
-__global__ void k_status_reset(int *status, int spec) {
+// Several requests' workspaces in one launch: block b resets item b.
+struct ResetArgs {
+    int *status[kMaxAuxBatch];
+};
+__global__ void k_status_reset(ResetArgs a, int spec) {
     const int i = threadIdx.x;
+    int *status = a.status[blockIdx.x];
     if (i < kStatusWords) status[i] = (i == kStatusSpecWord && !spec) ? 0 : INT_MAX;
+    if (i == kStatusWords) status[kFrobCounterWord] = 0;
 }
+
+__global__ void k_frob_counter_reset(int *status) { status[kFrobCounterWord] = 0; }
 
 __global__ void k_status_copy(const int *status, int *info) {
     if (threadIdx.x == 0) info[0] = status[0] == INT_MAX ? 0 : status[0];
 }
 
-// 2-D grid-stride conversion of an (m x n) column-major view.
+// Items of a batched launch: item q owns the blocks from start[q] on.
+template <typename Item>
+struct AuxArgs {
+    Item item[kMaxAuxBatch];
+    int32_t start[kMaxAuxBatch];
+    int32_t count;
+};
+
+template <typename Item>
+__device__ inline int aux_member(const AuxArgs<Item> &a) {
+    int q = 0;
+    while (q + 1 < a.count && (int)blockIdx.x >= a.start[q + 1]) ++q;
+    return q;
+}
+
+// Conversion of (m x n) column-major views: a wave takes 1024 rows of a column
+// at a time (16 elements a lane in flight).
 template <typename S, typename D>
-__global__ void __launch_bounds__(256)
-    k_convert(const S *__restrict__ src, int64_t lds, D *__restrict__ dst, int64_t ldd, int64_t m,
-              int64_t n) {
-    for (int64_t j = blockIdx.y; j < n; j += gridDim.y)
-        for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < m;
-             i += (int64_t)gridDim.x * 256)
-            dst[i + j * ldd] = (D)src[i + j * lds];
+__device__ inline void convert_unit(const ConvItem &it, int64_t u, int lane) {
+    const int64_t segs = (it.m + 1023) / 1024, j = u / segs, i0 = (u % segs) * 1024 + lane;
+    if (j >= it.n) return;
+    const S *src = static_cast<const S *>(it.src) + j * it.lds;
+    D *dst = static_cast<D *>(it.dst) + j * it.ldd;
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+        if (i0 + 64 * q < it.m) dst[i0 + 64 * q] = (D)src[i0 + 64 * q];
+}
+__global__ void __launch_bounds__(256) k_convert(AuxArgs<ConvItem> a) {
+    const int q = aux_member(a);
+    const int64_t u = (int64_t)((int)blockIdx.x - a.start[q]) * 4 + (threadIdx.x >> 6);
+    if (a.item[q].to_f32)
+        convert_unit<double, float>(a.item[q], u, threadIdx.x & 63);
+    else
+        convert_unit<float, double>(a.item[q], u, threadIdx.x & 63);
 }
 
 // dst (n x m, ldd) = src (m x n, lds)^T.  A workgroup moves one 64 x 64 tile
@@ -86,92 +120,122 @@ __global__ void __launch_bounds__(256) k_fill_zero(double *__restrict__ d, int64
             d[i + j * ld] = 0.0;
 }
 
-// Per-block partial sums of squares over whole columns (fixed assignment of
-// columns to blocks and fixed in-block order: the result does not depend on
-// scheduling).
-__global__ void __launch_bounds__(256)
-    k_frob_partial(const double *__restrict__ src, int64_t ld, int64_t m, int64_t n,
-                   double *__restrict__ partials) {
-    __shared__ double red[256];
-    double s = 0.0;
-    for (int64_t j = blockIdx.x; j < n; j += gridDim.x)
-        for (int64_t i = threadIdx.x; i < m; i += 256) {
-            const double v = src[i + j * ld];
-            s = fma(v, v, s);
-        }
-    red[threadIdx.x] = s;
+// Sums of squares of (m x n) views and what the refinement makes of them, in
+// one launch for up to kMaxAuxBatch views.  Each wave sums whole columns (fixed
+// assignment of columns to waves and fixed in-block order); the block of a view
+// that finishes last, told by a counter in front of the view's partials that it
+// sets back to 0, adds the partials in a fixed order, so the result does not
+// depend on scheduling or on the other views.  Then
+//   kFrobOnly   nothing more;
+//   kFrobCheck  refinement monitor: flags divergence when |R_j|_F did not
+//               decrease (out is norms + j);
+//   kFrobFinal  acceptance of a refined inverse, out = norms + 3 = |X|^2 being
+//               the last of the three: flags divergence unless rho = |R|_F /
+//               (|A|_F |X|_F) <= kNsTol (norms[2] = |R|^2, norms[0] = |A|^2; a
+//               NaN anywhere fails the test).
+// Three launches for each norm before (partials, sum, check): 14 mixed requests
+// of a batch spent 680 us on 70 norms, 230 us now; order 2048 12 to 17 us a
+// norm, 11 us now.
+__device__ inline double block_sum(double s) {
+    __shared__ double red[4];
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) s += __shfl_xor(s, w);
+    __syncthreads();  // the previous sum has been read
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) partials[blockIdx.x] = red[0];
+    return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-__global__ void __launch_bounds__(256) k_frob_final(const double *__restrict__ partials, int np,
-                                                      double *__restrict__ out) {
-    __shared__ double red[256];
+__global__ void __launch_bounds__(256) k_frob(AuxArgs<FrobItem> a) {
+    __shared__ bool last;
+    const int q = aux_member(a);
+    const FrobItem &it = a.item[q];
+    const int b = (int)blockIdx.x - a.start[q], nb = it.blocks;
+    const int64_t m = it.m, n = it.n;
     double s = 0.0;
-    for (int i = threadIdx.x; i < np; i += 256) s += partials[i];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
+    // a wave takes a column, 64 rows at a time
+    for (int64_t c = b * 4 + (threadIdx.x >> 6); c < n; c += nb * 4) {
+        const double *col = it.src + c * it.ld;
+#pragma unroll 8
+        for (int64_t i = threadIdx.x & 63; i < m; i += 64) s = fma(col[i], col[i], s);
     }
-    if (threadIdx.x == 0) *out = red[0];
-}
-
-// Refinement monitor: flags divergence when |R_j|_F did not decrease.
-__global__ void k_ns_check(const double *norms, int j, int *status) {
-    if (threadIdx.x == 0 && j > 0 && !(norms[j] < norms[j - 1])) status[0] = kStatusNsDiverged;
-}
-
-// Acceptance of a refined inverse: flags divergence unless
-// rho = |R|_F / (|A|_F |X|_F) <= tol (a NaN anywhere fails the test).
-__global__ void k_ns_final(const double *r2, const double *a2, const double *x2, double tol,
-                           int *status) {
+    s = block_sum(s);
+    double *const partials = it.partials;
+    unsigned *const counter = reinterpret_cast<unsigned *>(partials) - 2;
     if (threadIdx.x == 0) {
-        const double rho = sqrt(*r2) / (sqrt(*a2) * sqrt(*x2));
-        if (!(rho <= tol)) status[0] = kStatusNsDiverged;
+        // The partial is stored device-coherently and has arrived before the
+        // block is counted; nothing else is handed over, so no fence (which
+        // would write back the whole L2) is needed.
+        __hip_atomic_store(partials + b, s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        last = (int)__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nb - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    s = 0.0;
+    for (int i = threadIdx.x; i < nb; i += 256)
+        s += __hip_atomic_load(partials + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s = block_sum(s);
+    if (threadIdx.x != 0) return;
+    __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *it.out = s;
+    if (it.then == kFrobCheck && it.j > 0 && !(s < it.out[-1])) *it.status = kStatusNsDiverged;
+    if (it.then == kFrobFinal) {
+        const double rho = sqrt(it.out[-1]) / (sqrt(it.out[-3]) * sqrt(s));
+        if (!(rho <= kNsTol)) *it.status = kStatusNsDiverged;
     }
 }
 
-template <typename S, typename D>
-hipError_t convert(const S *src, int64_t lds, D *dst, int64_t ldd, int64_t m, int64_t n,
-                   hipStream_t s) {
-    if (m <= 0 || n <= 0) return hipSuccess;
-    const int64_t bx = (m + 255) / 256;
-    dim3 grid((unsigned)(bx < 64 ? bx : 64), (unsigned)(n < 4096 ? n : 4096));
-    hipLaunchKernelGGL((k_convert<S, D>), grid, dim3(256), 0, s, src, lds, dst, ldd, m, n);
+// Launches kernel k over the items, units blocks each.
+template <typename Item, typename U>
+hipError_t aux_launch(void (*k)(AuxArgs<Item>), const Item *items, int count, U blocks, hipStream_t s) {
+    if (count < 0 || count > kMaxAuxBatch) return hipErrorInvalidValue;
+    AuxArgs<Item> a{};
+    int64_t total = 0;
+    for (int q = 0; q < count; ++q) {
+        if (items[q].m <= 0 || items[q].n <= 0) continue;
+        a.item[a.count] = items[q];
+        a.start[a.count++] = (int32_t)total;
+        total += blocks(a.item[a.count - 1]);
+        if (total > INT_MAX) return hipErrorInvalidValue;
+    }
+    if (total == 0) return hipSuccess;
+    hipLaunchKernelGGL(k, dim3((unsigned)total), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t status_reset(int *status, bool spec, hipStream_t s) {
-    hipLaunchKernelGGL(k_status_reset, dim3(1), dim3(64), 0, s, status, spec ? 1 : 0);
+hipError_t status_reset(int *const *status, int count, bool spec, hipStream_t s) {
+    if (count < 1 || count > kMaxAuxBatch) return hipErrorInvalidValue;
+    ResetArgs a{};
+    for (int q = 0; q < count; ++q) a.status[q] = status[q];
+    hipLaunchKernelGGL(k_status_reset, dim3((unsigned)count), dim3(64), 0, s, a, spec ? 1 : 0);
     return hipGetLastError();
 }
+
+hipError_t status_reset(int *status, bool spec, hipStream_t s) { return status_reset(&status, 1, spec, s); }
 
 hipError_t status_copy(const int *status, int *info, hipStream_t s) {
     hipLaunchKernelGGL(k_status_copy, dim3(1), dim3(64), 0, s, status, info);
     return hipGetLastError();
 }
 
+hipError_t convert(const ConvItem *items, int count, hipStream_t s) {
+    return aux_launch(k_convert, items, count,
+                      [](const ConvItem &it) { return ((it.m + 1023) / 1024 * it.n + 3) / 4; }, s);
+}
+
 hipError_t cast_f64_to_f32(const double *src, int64_t lds, float *dst, int64_t ldd, int64_t m,
                            int64_t n, hipStream_t s) {
-    return convert<double, float>(src, lds, dst, ldd, m, n, s);
+    const ConvItem it{src, dst, lds, ldd, m, n, 1};
+    return convert(&it, 1, s);
 }
 
 hipError_t cast_f32_to_f64(const float *src, int64_t lds, double *dst, int64_t ldd, int64_t m,
                            int64_t n, hipStream_t s) {
-    return convert<float, double>(src, lds, dst, ldd, m, n, s);
-}
-
-hipError_t copy_f64(const double *src, int64_t lds, double *dst, int64_t ldd, int64_t m,
-                    int64_t n, hipStream_t s) {
-    return convert<double, double>(src, lds, dst, ldd, m, n, s);
+    const ConvItem it{src, dst, lds, ldd, m, n, 0};
+    return convert(&it, 1, s);
 }
 
 hipError_t fill_zero_f64(double *d, int64_t ld, int64_t m, int64_t n, hipStream_t s) {
@@ -200,30 +264,32 @@ hipError_t transpose_f64(const double *src, int64_t lds, double *dst, int64_t ld
     return hipGetLastError();
 }
 
-hipError_t ns_check(const double *norms, int j, int *status, hipStream_t s) {
-    hipLaunchKernelGGL(k_ns_check, dim3(1), dim3(64), 0, s, norms, j, status);
-    return hipGetLastError();
-}
-
-hipError_t ns_final(const double *r2, const double *a2, const double *x2, double tol, int *status,
-                    hipStream_t s) {
-    hipLaunchKernelGGL(k_ns_final, dim3(1), dim3(64), 0, s, r2, a2, x2, tol, status);
-    return hipGetLastError();
-}
-
+// Blocks of a norm: one per 32 KB (16 loads a lane), at most kNormBlocks,
+// because counting a block takes about 20 ns, and at most one per column
+// quartet.
 int frob_partials_count(int64_t m, int64_t n) {
-    (void)m;
-    return (int)(n < kNormBlocks ? (n > 0 ? n : 1) : kNormBlocks);
+    const int64_t b = std::min<int64_t>({(m * n + 4095) / 4096, (n + 3) / 4, kNormBlocks});
+    return (int)std::max<int64_t>(b, 1);
+}
+
+hipError_t frob_counter_reset(int *status, hipStream_t s) {
+    hipLaunchKernelGGL(k_frob_counter_reset, dim3(1), dim3(1), 0, s, status);
+    return hipGetLastError();
+}
+
+hipError_t frob(const FrobItem *items, int count, hipStream_t s) {
+    return aux_launch(k_frob, items, count,
+                      [](FrobItem &it) {
+                          it.blocks = frob_partials_count(it.m, it.n);
+                          return (int64_t)it.blocks;
+                      },
+                      s);
 }
 
 hipError_t frob2(const double *src, int64_t ld, int64_t m, int64_t n, double *partials,
                  double *out, hipStream_t s) {
-    const int np = frob_partials_count(m, n);
-    hipLaunchKernelGGL(k_frob_partial, dim3(np), dim3(256), 0, s, src, ld, m, n, partials);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_frob_final, dim3(1), dim3(256), 0, s, partials, np, out);
-    return hipGetLastError();
+    const FrobItem it{src, ld, m, n, partials, out, nullptr, kFrobOnly, 0, 0};
+    return frob(&it, 1, s);
 }
 
 }  // namespace spin

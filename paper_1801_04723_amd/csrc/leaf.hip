@@ -498,13 +498,17 @@ __device__ __attribute__((always_inline)) inline bool gj_blocked(const LeafArgs 
             for (int v = 0; v < 4; ++v) {
                 const int row = 16 * (w + NW * i) + rr, col = 16 * c + 4 * v + g;
                 // beyond the last step the block continues as the identity: its
-                // steps leave every other value as it is
+                // steps leave every other value as it is.  A whole leaf's loads
+                // outside the block go to its first entry: in a branch, an FP32
+                // leaf would wait for each load before its conversion (order
+                // 128: 55 -> 47 us).
+                const bool in = row < L && col < nb;
                 double x = (col >= nb && row == k0 + col) ? 1.0 : 0.0;
-                if (row < L && col < nb) {
-                    if (WHOLE)
-                        x = (double)static_cast<const TI *>(a.in)[row + (int64_t)col * a.ldi];
-                    else
-                        x = src[row + (int64_t)(k0 + col) * lds];
+                if (WHOLE) {
+                    const double v0 = (double)*(static_cast<const TI *>(a.in) + (in ? row + (int64_t)col * a.ldi : 0));
+                    x = in ? v0 : x;
+                } else if (in) {
+                    x = src[row + (int64_t)(k0 + col) * lds];
                 }
                 acc[i][c][v] = x;
             }

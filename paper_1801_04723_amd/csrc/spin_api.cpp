@@ -469,6 +469,7 @@ int ws_acquire(hipStream_t s, size_t bytes, Workspace **out) {
             // that spin_info still reports it after a later call grew the
             // workspace without writing them (spin_residual)
             hipError_t e = hipMemcpyAsync(p, w.base, 256, hipMemcpyDeviceToDevice, s);
+            if (e == hipSuccess) e = frob_counter_reset(static_cast<int *>(p), s);
             if (e == hipSuccess) e = hipStreamSynchronize(s);
             if (e != hipSuccess) {
                 (void)hipGetLastError();
@@ -863,9 +864,8 @@ int spin_invert_mixed(const double *A, int64_t n, int64_t lda, double *Ainv, int
             e = refine_product(A, lda, xc, ldc, 1, nullptr, 1, R, n, qs, &li);
             if (g_trace_on) trace_cb(&ctx, li, 1);
             if (e != hipSuccess) return e;
-            e = frob2(R, n, n, n, parts, norms + j, qs);
-            if (e != hipSuccess) return e;
-            e = ns_check(norms, j, status + 1, qs);
+            const FrobItem fr{R, n, n, n, parts, norms + j, status + 1, kFrobCheck, j, 0};
+            e = frob(&fr, 1, qs);
             if (e != hipSuccess) return e;
             // X' = X + X R
             if (g_trace_on) trace_cb(&ctx, li, 0);
@@ -883,8 +883,8 @@ int spin_invert_mixed(const double *A, int64_t n, int64_t lda, double *Ainv, int
             if (g_trace_on) trace_cb(&ctx, li, 1);
             if (e == hipSuccess) e = frob2(R, n, n, n, parts, misc + 2, qs);
             if (e == hipSuccess) e = frob2(A, lda, n, n, parts, misc + 0, qs);
-            if (e == hipSuccess) e = frob2(Ainv, ldx, n, n, parts, misc + 3, qs);
-            if (e == hipSuccess) e = ns_final(misc + 2, misc + 0, misc + 3, kNsTol, status + 1, qs);
+            const FrobItem fr{Ainv, ldx, n, n, parts, misc + 3, status + 1, kFrobFinal, 0, 0};
+            if (e == hipSuccess) e = frob(&fr, 1, qs);
             if (e != hipSuccess) return e;
         }
         return hipSuccess;

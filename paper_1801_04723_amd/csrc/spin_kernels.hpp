@@ -118,13 +118,19 @@ hipError_t leaf_batch_launch(const LeafItem *items, int count, DType dt, hipStre
 // atomically; word kStatusSpecWord is the leaves' speculation switch
 // (nonzero: try the speculative elimination first).
 constexpr int kStatusWords = 3;
+// Int of a workspace that counts the finished blocks of a norm (the 8 bytes
+// before the norms' partials); 0 between launches.
+constexpr int kFrobCounterWord = (4096 - 8) / 4;
 constexpr int kStatusSpecWord = 2;
+// Most items of one batched auxiliary launch (requests of a serving tick);
+// each item's result is the one it gets alone.
+constexpr int kMaxAuxBatch = 32;
+hipError_t status_reset(int *const *status, int count, bool spec, hipStream_t s);
 hipError_t status_reset(int *status, bool spec, hipStream_t s);
 // *info = the pivot status word (0 when it holds "no event"), by a kernel.
 hipError_t status_copy(const int *status, int *info, hipStream_t s);
 // Value written to the refinement status word on divergence (SPIN_NS_DIVERGED).
 constexpr int kStatusNsDiverged = -100;
-hipError_t ns_check(const double *norms, int j, int *status, hipStream_t s);
 // Residual bound a refined inverse must meet: rho = |A X - I|_F / (|A|_F
 // |X|_F) <= kNsTol after the refinement steps, else the refinement status
 // word gets SPIN_NS_DIVERGED.
@@ -136,14 +142,18 @@ constexpr int kRefineModuli = 14;
 // k products of symmetric residues (|r| <= 128) in int32, exact while
 // k 128^2 < 2^31.
 constexpr int64_t kOzakiMaxK = 131071;
-hipError_t ns_final(const double *r2, const double *a2, const double *x2, double tol, int *status,
-                    hipStream_t s);
+// Conversion of an (m x n) view, FP64 -> FP32 (to_f32) or FP32 -> FP64.
+struct ConvItem {
+    const void *src;
+    void *dst;
+    int64_t lds, ldd, m, n;
+    int32_t to_f32;
+};
+hipError_t convert(const ConvItem *items, int count, hipStream_t s);
 hipError_t cast_f64_to_f32(const double *src, int64_t lds, float *dst, int64_t ldd, int64_t m,
                            int64_t n, hipStream_t s);
 hipError_t cast_f32_to_f64(const float *src, int64_t lds, double *dst, int64_t ldd, int64_t m,
                            int64_t n, hipStream_t s);
-hipError_t copy_f64(const double *src, int64_t lds, double *dst, int64_t ldd, int64_t m,
-                    int64_t n, hipStream_t s);
 // dst (n x m, ldd) = src (m x n, lds)^T; the views must not overlap.
 hipError_t transpose_f64(const double *src, int64_t lds, double *dst, int64_t ldd, int64_t m,
                          int64_t n, hipStream_t s);
@@ -185,10 +195,27 @@ int ozaki_beta(int count, int64_t k);
 size_t ozaki_workspace_bytes(int64_t m, int64_t n, int64_t k, int count);
 hipError_t ozaki_product(const OzakiProb &p, void *ws, hipStream_t s);
 
-// Sum of squares of an (m x n) FP64 view, deterministic two-pass reduction:
-// partials (>= frob_partials_count(m, n) doubles) then one block writes *out.
+// Sum of squares of an (m x n) FP64 view, deterministic: partials (>=
+// frob_partials_count(m, n) doubles behind the counter at kFrobCounterWord of
+// the same workspace) and one sum in a fixed order to *out; then
+//   kFrobCheck: SPIN_NS_DIVERGED into *status unless out[0] < out[-1] (j > 0);
+//   kFrobFinal: the same unless rho = sqrt(out[-1]) / (sqrt(out[-3])
+//               sqrt(out[0])) <= kNsTol.
+enum FrobThen : int32_t { kFrobOnly, kFrobCheck, kFrobFinal };
+struct FrobItem {
+    const double *src;
+    int64_t ld, m, n;
+    double *partials, *out;
+    int *status;
+    FrobThen then;
+    int32_t j;
+    int32_t blocks;  // set by the launch
+};
 int frob_partials_count(int64_t m, int64_t n);
+hipError_t frob(const FrobItem *items, int count, hipStream_t s);
 hipError_t frob2(const double *src, int64_t ld, int64_t m, int64_t n, double *partials,
                  double *out, hipStream_t s);
+// Zeroes the counter of a workspace that starts at status.
+hipError_t frob_counter_reset(int *status, hipStream_t s);
 
 }  // namespace spin

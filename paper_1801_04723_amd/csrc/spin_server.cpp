@@ -82,7 +82,7 @@ class PoolAllocator {
 
 // --------------------------------------------------------------- steps ----
 enum StepKind { STEP_GEMM = 0, STEP_LEAF = 1, STEP_AUX = 2 };
-enum AuxOp { AUX_RESET, AUX_CAST_IN, AUX_WIDEN, AUX_FROB, AUX_NSCHECK, AUX_TRANSPOSE, AUX_MIRROR, AUX_NSFINAL };
+enum AuxOp { AUX_RESET, AUX_CAST_IN, AUX_WIDEN, AUX_FROB, AUX_FROBCHECK, AUX_FROBFINAL, AUX_TRANSPOSE, AUX_MIRROR };
 
 // A mode with SPIN_SYMMETRIC runs the symmetric schedule of spin_invert_spd
 // with the mode's product flavour.
@@ -225,12 +225,10 @@ bool build_steps(Request &r, int64_t leaf, int ns_steps) {
         g.prob[0] = GemmProb{r.A, xc, nullptr, R, r.lda, ldc, 1, n, (int32_t)n, (int32_t)n,
                              (int32_t)n, 1, -1.0, 0.0};
         r.steps.push_back(g);
-        Step fr = aux_step(AUX_FROB);
+        Step fr = aux_step(AUX_FROBCHECK);
         fr.src = R, fr.lds = n, fr.m = n, fr.n = n, fr.norms = norms + j, fr.partials = parts;
+        fr.j = j, fr.status = status + 1;
         r.steps.push_back(fr);
-        Step ck = aux_step(AUX_NSCHECK);
-        ck.norms = norms, ck.j = j, ck.status = status + 1;
-        r.steps.push_back(ck);
         Step u;
         std::memset(&u, 0, sizeof(u));
         u.kind = STEP_GEMM;
@@ -255,37 +253,58 @@ bool build_steps(Request &r, int64_t leaf, int ns_steps) {
         const int64_t ld[3] = {n, r.lda, r.ldx};
         const int slot[3] = {2, 0, 3};
         for (int q = 0; q < 3; ++q) {
-            Step fr = aux_step(AUX_FROB);
+            // the last one also accepts or rejects
+            Step fr = aux_step(q < 2 ? AUX_FROB : AUX_FROBFINAL);
             fr.src = src[q], fr.lds = ld[q], fr.m = n, fr.n = n, fr.norms = misc + slot[q];
-            fr.partials = parts;
+            fr.partials = parts, fr.status = status + 1;
             r.steps.push_back(fr);
         }
-        Step fin = aux_step(AUX_NSFINAL);
-        fin.norms = misc, fin.status = status + 1;
-        r.steps.push_back(fin);
     }
     return true;
 }
 
-hipError_t run_aux(const Step &s, hipStream_t st) {
-    switch (s.aux) {
-    case AUX_RESET: return status_reset(s.status, leaf_spec_enabled(), st);
-    case AUX_CAST_IN:
-        return cast_f64_to_f32(static_cast<const double *>(s.src), s.lds, static_cast<float *>(s.dst),
-                               s.ldd, s.m, s.n, st);
-    case AUX_WIDEN:
-        return cast_f32_to_f64(static_cast<const float *>(s.src), s.lds, static_cast<double *>(s.dst),
-                               s.ldd, s.m, s.n, st);
-    case AUX_FROB:
-        return frob2(static_cast<const double *>(s.src), s.lds, s.m, s.n, s.partials, s.norms, st);
-    case AUX_NSCHECK: return ns_check(s.norms, s.j, s.status, st);
-    case AUX_NSFINAL: return ns_final(s.norms + 2, s.norms + 0, s.norms + 3, kNsTol, s.status, st);
-    case AUX_TRANSPOSE:
-        return transpose_f64(static_cast<const double *>(s.src), s.lds, static_cast<double *>(s.dst),
-                             s.ldd, s.m, s.n, st);
-    case AUX_MIRROR: return mirror_lower_f64(static_cast<double *>(s.dst), s.ldd, s.m, st);
+// One auxiliary step of each of several requests, those of a kind in one
+// launch.  A request's steps stay in order, and each step's result does not
+// depend on the others in its launch.
+hipError_t run_aux(const std::vector<const Step *> &steps, hipStream_t st) {
+    std::vector<int *> reset;
+    std::vector<ConvItem> conv;
+    std::vector<FrobItem> fr;
+    hipError_t e = hipSuccess;
+    for (const Step *p : steps) {
+        const Step &s = *p;
+        switch (s.aux) {
+        case AUX_RESET: reset.push_back(s.status); break;
+        case AUX_CAST_IN:
+        case AUX_WIDEN:
+            conv.push_back(ConvItem{s.src, s.dst, s.lds, s.ldd, s.m, s.n, s.aux == AUX_CAST_IN});
+            break;
+        case AUX_FROB:
+        case AUX_FROBCHECK:
+        case AUX_FROBFINAL:
+            fr.push_back(FrobItem{static_cast<const double *>(s.src), s.lds, s.m, s.n, s.partials, s.norms, s.status,
+                                  s.aux == AUX_FROB        ? kFrobOnly
+                                  : s.aux == AUX_FROBCHECK ? kFrobCheck
+                                                           : kFrobFinal,
+                                  s.j, 0});
+            break;
+        case AUX_TRANSPOSE:
+            e = transpose_f64(static_cast<const double *>(s.src), s.lds, static_cast<double *>(s.dst), s.ldd, s.m,
+                              s.n, st);
+            break;
+        case AUX_MIRROR: e = mirror_lower_f64(static_cast<double *>(s.dst), s.ldd, s.m, st); break;
+        default: e = hipErrorInvalidValue;
+        }
+        if (e != hipSuccess) return e;
     }
-    return hipErrorInvalidValue;
+    auto all = [&](size_t n, auto launch) {
+        for (size_t i = 0; i < n && e == hipSuccess; i += kMaxAuxBatch)
+            e = launch(i, (int)std::min<size_t>(kMaxAuxBatch, n - i));
+    };
+    all(reset.size(), [&](size_t i, int c) { return status_reset(reset.data() + i, c, leaf_spec_enabled(), st); });
+    all(conv.size(), [&](size_t i, int c) { return convert(conv.data() + i, c, st); });
+    all(fr.size(), [&](size_t i, int c) { return frob(fr.data() + i, c, st); });
+    return e;
 }
 
 }  // namespace
@@ -421,14 +440,21 @@ int spin_server_tick(spin_server *s, spin_stream_t stream) {
             e = hipErrorInvalidValue;
             break;
         }
-        // leading auxiliary steps run now; then one product/leaf step joins the groups
-        while (r->next < r->steps.size() && e == hipSuccess) {
+    }
+    // leading auxiliary steps run now, one of every request at a time; then one
+    // product/leaf step joins the groups
+    while (e == hipSuccess) {
+        std::vector<const Step *> aux;
+        for (Request *r : s->active)
+            if (!r->done && r->next < r->steps.size() && r->steps[r->next].kind == STEP_AUX)
+                aux.push_back(&r->steps[r->next++]);
+        if (aux.empty()) break;
+        e = run_aux(aux, st);
+    }
+    for (Request *r : s->active) {
+        if (r->done || e != hipSuccess) continue;
+        if (r->next < r->steps.size()) {
             const Step &stp = r->steps[r->next];
-            if (stp.kind == STEP_AUX) {
-                e = run_aux(stp, st);
-                ++r->next;
-                continue;
-            }
             if (stp.kind == STEP_GEMM) {
                 for (int q = 0; q < stp.nprob; ++q) g[(int)stp.dt].push_back(stp.prob[q]);
             } else if (stp.leaf.L <= 128) {
@@ -440,7 +466,6 @@ int spin_server_tick(spin_server *s, spin_stream_t stream) {
                 if (e == hipSuccess && leaf_fills_exchange(stp.leaf.L)) r->exch_filled = true;
             }
             ++r->next;
-            break;
         }
         if (r->next >= r->steps.size()) finished.push_back(r);
     }
