@@ -361,16 +361,15 @@ __device__ __attribute__((always_inline)) inline void gj2d_run(const LeafArgs &a
 // straight into its chain.
 //
 // What bounds it: FP64 vector and matrix instructions share one unit per
-// SIMD, and a block step of a 128-order leaf spends about 12 000 cycles there
-// on the busiest one: panels 3 100 (16 x 24 instructions of a lone wave), the
-// chain 5 000 (16 x 37 dependent instructions), the MFMAs of the two waves on
-// the chain's SIMD about 3 500.  Placing the chain wave's own MFMAs between
+// SIMD, and the panels (16 x 24 instructions of a lone wave, about 3 100
+// cycles), the chain (16 x 37 dependent instructions, 5 000 cycles) and the
+// MFMAs follow each other there.  Placing the chain wave's own MFMAs between
 // its steps gained nothing for the same reason.  Whole inversions of one leaf
 // (launches included), against the earlier kernels with a barrier or a flag
-// per step: order 64 30 -> 20 us, 128 88 -> 50 us, 257 325 -> 247 us, 512
-// 758 -> 547 us; full panels of orders 129 .. 256 stay with leaf_duo, whose
-// two CUs take 29 us against 34 us here (22 us of steps, the rest loads and
-// stores of one CU).
+// per step: order 257 325 -> 247 us, 512 758 -> 547 us; full panels of orders
+// 129 .. 256 stay with leaf_duo, whose two CUs take 29 us against 34 us here
+// (22 us of steps, the rest loads and stores of one CU); whole leaves have
+// gj_ahead.
 
 // Pivots whose reciprocal the chain forms without the scaling and fix-up of
 // the FP64 division: for these the division leaves divisor and quotient
@@ -477,16 +476,16 @@ __device__ __attribute__((always_inline)) inline void col_steps(double (&y)[16],
         ...);
 }
 
-template <int NW, int RB, int NC, bool WHOLE, typename TI, typename TO>
+template <int NW, int RB, int NC>
 __device__ __attribute__((always_inline)) inline bool gj_blocked(const LeafArgs &a, double *sm) {
     using S = BlkLds<NW, RB, NC>;
     constexpr int NT = 64 * NW;
     const int t = threadIdx.x, lane0 = t & 63, lane = lane0, rr = lane & 15, g = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int L = a.L, k0 = WHOLE ? 0 : a.k0, nb = WHOLE ? a.L : a.nb;
+    const int L = a.L, k0 = a.k0, nb = a.nb;
     if ((k0 & 15) != 0 || nb < 1 || nb > S::kCols || L > S::kRows) return false;  // the same in every thread
-    const double *src = WHOLE ? nullptr : (a.in ? static_cast<const double *>(a.in) : a.Z);
-    const int64_t lds = WHOLE ? 0 : (a.in ? a.ldi : a.ldz);
+    const double *src = a.in ? static_cast<const double *>(a.in) : a.Z;
+    const int64_t lds = a.in ? a.ldi : a.ldz;
 
     // lane l holds row 16 (w + NW i) + l % 16 of columns 16 c + 4 v + l / 16
     d4_t acc[RB][NC];
@@ -498,23 +497,14 @@ __device__ __attribute__((always_inline)) inline bool gj_blocked(const LeafArgs 
             for (int v = 0; v < 4; ++v) {
                 const int row = 16 * (w + NW * i) + rr, col = 16 * c + 4 * v + g;
                 // beyond the last step the block continues as the identity: its
-                // steps leave every other value as it is.  A whole leaf's loads
-                // outside the block go to its first entry: in a branch, an FP32
-                // leaf would wait for each load before its conversion (order
-                // 128: 55 -> 47 us).
-                const bool in = row < L && col < nb;
+                // steps leave every other value as it is
                 double x = (col >= nb && row == k0 + col) ? 1.0 : 0.0;
-                if (WHOLE) {
-                    const double v0 = (double)*(static_cast<const TI *>(a.in) + (in ? row + (int64_t)col * a.ldi : 0));
-                    x = in ? v0 : x;
-                } else if (in) {
-                    x = src[row + (int64_t)(k0 + col) * lds];
-                }
+                if (row < L && col < nb) x = src[row + (int64_t)(k0 + col) * lds];
                 acc[i][c][v] = x;
             }
     // Panels of up to 256 rows load the pivot rows of the outside columns (Q)
     // here, so that the loads complete during the elimination.
-    constexpr bool QPRE = !WHOLE && RB <= 2;
+    constexpr bool QPRE = RB <= 2;
     constexpr int QPT = QPRE ? (S::kRows - 64) / NW : 1;
     const int nout = L - nb;
     double qv[QPT];
@@ -526,7 +516,7 @@ __device__ __attribute__((always_inline)) inline bool gj_blocked(const LeafArgs 
         }
     }
     bool viol = false;
-    if (!WHOLE && k0 > 0) {
+    if (k0 > 0) {
         // the rows before the panel must be the used ones and no other
         for (int row = t; row < L; row += NT)
             if ((a.used[row] != 0) != (row < k0)) viol = true;
@@ -700,38 +690,452 @@ __device__ __attribute__((always_inline)) inline bool gj_blocked(const LeafArgs 
                 const int row = 16 * (w + NW * i) + sr, col = 16 * c + 4 * v + sg;
                 if (row < L && col < nb) {
                     const double x = acc[i][c][v];
-                    if (WHOLE) {
-                        static_cast<TO *>(a.out)[row + (int64_t)col * a.ldo] = (TO)x;
-                    } else {
-                        a.Z[row + (int64_t)(k0 + col) * a.ldz] = x;
-                        a.Up[row + (int64_t)col * L] = x - ((row == k0 + col) ? 1.0 : 0.0);
-                    }
+                    a.Z[row + (int64_t)(k0 + col) * a.ldz] = x;
+                    a.Up[row + (int64_t)col * L] = x - ((row == k0 + col) ? 1.0 : 0.0);
                 }
             }
-    if constexpr (!WHOLE) {
-        for (int c = t; c < nb; c += NT) a.rsel[k0 + c] = k0 + c;
-        for (int row = t; row < L; row += NT) {
-            const bool piv = row >= k0 && row < k0 + nb;
-            if (k0 == 0)
-                a.used[row] = piv ? 1 : 0;
-            else if (piv)
-                a.used[row] = 1;
-        }
-        if constexpr (QPRE) {
+    for (int c = t; c < nb; c += NT) a.rsel[k0 + c] = k0 + c;
+    for (int row = t; row < L; row += NT) {
+        const bool piv = row >= k0 && row < k0 + nb;
+        if (k0 == 0)
+            a.used[row] = piv ? 1 : 0;
+        else if (piv)
+            a.used[row] = 1;
+    }
+    if constexpr (QPRE) {
 #pragma unroll
-            for (int q = 0; q < QPT; ++q) {
-                const int j = w + NW * q, gj = j < k0 ? j : j + nb;
-                if (lane < nb && j < nout) a.Q[lane + (int64_t)gj * nb] = qv[q];
-            }
-        } else {
+        for (int q = 0; q < QPT; ++q) {
+            const int j = w + NW * q, gj = j < k0 ? j : j + nb;
+            if (lane < nb && j < nout) a.Q[lane + (int64_t)gj * nb] = qv[q];
+        }
+    } else {
 #pragma unroll 8
-            for (int j = w; j < nout; j += NW) {
-                const int gj = j < k0 ? j : j + nb;
-                if (lane < nb) a.Q[lane + (int64_t)gj * nb] = src[(k0 + lane) + (int64_t)gj * lds];
-            }
+        for (int j = w; j < nout; j += NW) {
+            const int gj = j < k0 ? j : j + nb;
+            if (lane < nb) a.Q[lane + (int64_t)gj * nb] = src[(k0 + lane) + (int64_t)gj * lds];
         }
     }
     return true;
+}
+
+// ------------------------------------------ blocked tier, chain ahead ---
+// gj_blocked for whole leaves, with a role for each wave and the serial chain
+// one block step ahead.  Block step b, between the same barriers:
+//   panels  one lane per row and one per column take the steps through the
+//           panels, but only as far as the multipliers F and the scaled pivot
+//           rows R need, which is half the updates; the chain wave does the
+//           same for the 16 rows and columns of the next diagonal block;
+//   update  four MFMAs for every 16 x 16 block; meanwhile the chain wave
+//           applies the block step to the next diagonal block and runs its
+//           chain.
+// The other half of the panels' updates is left to the matrix cores: a value
+// of the block column restarts at 0 in its own step, one of the pivot rows at
+// its scaled value, so the later steps are an MFMA chain from there, with 0
+// for the steps before (they add a zero to a value that is not -0).  The
+// operations on each element and their order stay gj_blocked's, and so the
+// search's; a multiplier or scaled entry that is not finite, whose product with
+// those zeros would be NaN, goes to the search.
+//
+// What bounds it (cycles per block step): order 128 fills the FP64 units, the
+// panels 2 700 and then 80 MFMAs of 64 cycles on a SIMD, 7 800 with the loads
+// before and the publication after them, the chain (2 100 + 4 600) beside
+// them; order 64 waits for the chain wave, 6 700.  Each role keeps a loop of
+// its own because the compiler spills where one wave's registers are live
+// through another's code.  Whole inversions of one leaf, launches included,
+// against gj_blocked: order 33 16.2 -> 14.4 us, 64 20.1 -> 17.5, 80 30.0 ->
+// 27.3, 100 42.7 -> 37.7, 128 50 -> 43.7.
+template <int N>
+struct AheadLds {
+    // The pitches spread rows read along a lane group's 16 lanes (kLd, and kPrLd
+    // for columns too) over the banks.
+    static constexpr int kLd = N + 16, kPrLd = N + 18, kMLd = 17, kMini = 16 * kMLd;
+    static constexpr int oPc = 0;                        // block column b [16][kLd]
+    static constexpr int oF = oPc + 16 * kLd;            // F [16][kLd]
+    static constexpr int oPr = oF + 16 * kLd;            // row block b [16][kPrLd]
+    static constexpr int oR = oPr + 16 * kPrLd;          // R [16][kPrLd], and from column N block column b's multiplicand
+    static constexpr int oStart = oR + 16 * kPrLd;       // where row block b's values start in the update [16][kPrLd]
+    static constexpr int oDr = oStart + 16 * kPrLd;      // pivot rows inside a diagonal block [2][256]
+    static constexpr int oDm = oDr + 512;                // its active columns [2][256]
+    static constexpr int oMini = oDm + 512;              // the next diagonal block's part of the panels, then of F
+                                                         // and R [2][2][kMini]
+    static constexpr int oPub = oMini + 4 * kMini;       // diagonal block before its last update [2][256]
+    static constexpr int oNew = oPub + 512;              // diagonal block after its chain [2][256]
+    static constexpr int oDump = oNew + 512;             // unwanted stores of the chain
+    static constexpr int kDoubles = oDump + 256;
+};
+
+// A wave's part.  Waves go to the four SIMDs in turn; wave 0 is the chain's,
+// and its SIMD gets the least of the rest.
+struct AheadRole {
+    int row, c0;  // row block and first column block held
+    int task;     // 64 rows (task < N / 64) or columns of the panels, or -1
+};
+constexpr int ahead_waves(int N) { return N == 64 ? 6 : 12; }
+constexpr int ahead_checks(int N) { return N == 64 ? 4 : 8; }  // the wave of the diagonal block's checks
+__device__ inline AheadRole ahead_role(int N, int w) {
+    if (N == 64) return {w == 5 ? 3 : w - 1, 0, w == 2 || w == 3 ? w - 2 : -1};
+    if (w < 4) return {w - 1, 0, -1};
+    if (w >= 5 && w < 8) return {w - 2, 0, -1};
+    const int h = w == 4 ? 3 : w - 9;  // the last two row blocks in halves
+    return {6 + (h >> 1), 4 * (h & 1), h};
+}
+
+// Four of fmac_rows' updates, j = J .. J + 3.
+template <int J>
+__device__ inline void fmac_quad(double &x0, double &x1, double &x2, double &x3, double r, double f) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %0, %4, -%5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %1, %4, -%5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %2, %4, -%5 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %3, %4, -%5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+        : "+v"(x0), "+v"(x1), "+v"(x2), "+v"(x3)
+        : "v"(r), "v"(f), "n"(J), "n"(J + 1), "n"(J + 2), "n"(J + 3));
+}
+
+// Step K's updates of the entries after K: x[j] -= r[lane j] * f.
+template <int K>
+__device__ __attribute__((always_inline)) inline void half_step(double (&x)[16], double r, double f) {
+    double t[4] = {0.0, 0.0, 0.0, 0.0};  // for entries up to K
+    static_for<4>([&](auto q) {
+        constexpr int J = 4 * q;
+        if constexpr (J > K)
+            fmac_quad<J>(x[J], x[J + 1], x[J + 2], x[J + 3], r, f);
+        else if constexpr (J + 3 > K)
+            fmac_quad<J>(t[0], J + 1 > K ? x[J + 1] : t[1], J + 2 > K ? x[J + 2] : t[2], x[J + 3], r, f);
+    });
+}
+
+// The multipliers of one row of the block column (x).  viol: a checked row
+// (kind 1) holds a candidate larger than a pivot or not finite, or another
+// (kind 0) a multiplier that is not finite, which every later value then is
+// not either; the block's own rows (kind 2) are not used.
+template <int... K>
+__device__ __attribute__((always_inline)) inline bool row_half(double (&x)[16], const double *dr16, double pd, double *F,
+                                                               int ld, int kind, std::integer_sequence<int, K...>) {
+    bool over = false;
+    double r[16] = {dr16[16 * K]...};
+    (
+        [&] {
+            const double f = x[K];
+            F[K * ld] = f;
+            over = over | !(fabs(f) <= fabs(row_bcast<K>(pd)));
+            half_step<K>(x, r[K], f);
+        }(),
+        ...);
+    return kind == 1 ? over : kind == 0 && !(fabs(x[15]) <= DBL_MAX);
+}
+
+// The scaled pivot rows' entries of one column of the block row (y), and where
+// the values of that column start in the update.
+template <int... K>
+__device__ __attribute__((always_inline)) inline bool col_half(double (&y)[16], const double *dm16, double id, double *R,
+                                                               double *start, int ld,
+                                                               std::integer_sequence<int, K...>) {
+    double m[16] = {dm16[16 * K]...};
+    (
+        [&] {
+            const double r = y[K] * row_bcast<K>(id);
+            R[K * ld] = r;
+            start[K * ld] = r + 0.0;
+            half_step<K>(y, m[K], r);
+        }(),
+        ...);
+    return !(fabs(y[15]) <= DBL_MAX);
+}
+
+// Both for the next diagonal block: lane groups 0, 2 its rows (id = 1), groups
+// 1, 3 its columns.
+template <int... K>
+__device__ __attribute__((always_inline)) inline void mini_half(double (&x)[16], const double (&r)[16], double id,
+                                                                std::integer_sequence<int, K...>) {
+    (
+        [&] {
+            x[K] *= row_bcast<K>(id);
+            half_step<K>(x, r[K], x[K]);
+        }(),
+        ...);
+}
+
+// A workgroup barrier for code that the waves reach on different paths.
+__device__ inline void wg_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// One wave's part of the panels of block step b; returns whether a check fails.
+template <int N>
+__device__ __attribute__((always_inline)) inline bool ahead_panel(double *sm, int L, int b, int task, int lane0) {
+    using S = AheadLds<N>;
+    constexpr auto kSteps = std::make_integer_sequence<int, 16>{};
+    const int lane = opaque(lane0), rr = lane & 15;
+    const double *const dr = sm + S::oDr + 256 * (b & 1), *const dm = sm + S::oDm + 256 * (b & 1);
+    double x[16];
+    if (task < N / 64) {
+        const int row = 64 * task + lane;
+        const int kind = row >= 16 * b + 16 ? (row < L ? 1 : 0) : row >= 16 * b ? 2 : 0;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) x[j] = sm[S::oPc + j * S::kLd + row];
+        return row_half(x, dr + rr, dm[17 * rr], sm + S::oF + row, S::kLd, kind, kSteps);
+    }
+    const int col = 64 * (task - N / 64) + lane;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) x[j] = sm[S::oPr + j * S::kPrLd + col];
+    return col_half(x, dm + rr, dr[17 * rr], sm + S::oR + col, sm + S::oStart + col, S::kPrLd,
+                    kSteps);
+}
+
+// A wave that holds NW blocks of row block me.row, from column block me.c0 on.
+template <int N, int NW, typename TI, typename TO>
+__device__ __attribute__((always_inline)) inline bool ahead_rows(const LeafArgs &a, double *sm, AheadRole me,
+                                                                 int lane0) {
+    using S = AheadLds<N>;
+    constexpr bool kTasks = NW == 4;
+    const int L = a.L, nblk = (L + 15) >> 4;
+    double *const F = sm + S::oF, *const R = sm + S::oR, *const pc = sm + S::oPc, *const pr = sm + S::oPr;
+    double *const pub = sm + S::oPub, *const nw = sm + S::oNew;
+
+    d4_t acc[NW];  // lane l holds row 16 me.row + l % 16 of columns 16 (me.c0 + i) + 4 v + l / 16
+    {
+        // beyond the last step the block continues as the identity; loads
+        // outside it go to its other entries, so that none waits in a branch
+        const int row = 16 * me.row + (lane0 & 15), c = 16 * me.c0 + (lane0 >> 4);
+        const TI *p = static_cast<const TI *>(a.in) + (row < L ? row : 0) + (c < L ? (int64_t)c * a.ldi : 0);
+#pragma unroll
+        for (int i = 0; i < NW; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int col = c + 16 * i + 4 * v;
+                const double x = (double)*p;
+                acc[i][v] = row < L && col < L ? x : (col >= L && row == col) ? 1.0 : 0.0;
+                p += col + 4 < L ? 4 * a.ldi : 0;
+            }
+    }
+    // Block column b (held in x), and its part in the next diagonal block's rows.
+    auto publish_col = [&](const d4_t &x, const int b, const int rr, const int g) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) pc[(4 * v + g) * S::kLd + 16 * me.row + rr] = x[v];
+        if (me.row == b + 1) {
+            double *const mini = sm + S::oMini + 2 * S::kMini * (b & 1);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) mini[S::kMLd * (4 * v + g) + rr] = x[v];
+        }
+    };
+    // Row block b, the next diagonal block and its columns' part.
+    auto publish_row = [&](const int b) {
+        const int ln = opaque(lane0), rr = ln & 15, g = ln >> 4;
+        double *const mini = sm + S::oMini + 2 * S::kMini * (b & 1);
+        const int ib = b - me.c0;
+        if (me.row == b) {
+            double *const p = pr + rr * S::kPrLd + 16 * me.c0 + g;
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) p[16 * i + 4 * v] = acc[i][v];
+        }
+        if (me.row == b || me.row == b + 1) {
+            static_for<NW>([&](auto i) {
+                if (i == ib + 1) {
+                    double *const m = me.row == b ? mini + S::kMini + S::kMLd * rr + g : pub + 256 * (~b & 1) + ln;
+                    const int ld = me.row == b ? 4 : 64;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) m[ld * v] = acc[i][v];
+                    branch_end<i>();
+                }
+            });
+        }
+    };
+    if (me.c0 == 0) publish_col(acc[0], 0, lane0 & 15, lane0 >> 4);
+    publish_row(0);
+    if (me.row == 0 && me.c0 == 0) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) pub[64 * v + lane0] = acc[0][v];
+    }
+    bool viol = false;
+    wg_barrier();
+    wg_barrier();
+#pragma unroll 1
+    for (int b = 0; b < nblk; ++b) {
+        wg_barrier();
+        if (kTasks && me.task >= 0) {
+            __builtin_amdgcn_s_setprio(3);
+            viol = viol | ahead_panel<N>(sm, L, b, me.task, lane0);
+            __builtin_amdgcn_s_setprio(0);
+        }
+        wg_barrier();
+        const int lane = opaque(lane0), rr = lane & 15, g = lane >> 4;
+        const int ib = b - me.c0, end = nblk - me.c0;
+        const bool own = me.row == b;
+        // block i's multiplicand
+        const double *const rl = R + g * S::kPrLd + rr;
+        auto load = [&](const int i, double (&f)[4]) {
+            const double *const r = rl + (i == ib ? N : 16 * (me.c0 + i));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) f[q] = r[4 * q * S::kPrLd];
+        };
+        double fa[4], fb[2][4];
+        load(0, fb[0]);
+        if (own) {
+            __builtin_amdgcn_s_setprio(2);  // it starts later than the others
+            const double *const m = sm + S::oDm + 256 * (b & 1) + rr, *const r0 = sm + S::oStart + rr * S::kPrLd + 16 * me.c0 + g;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) fa[q] = 4 * q + g > rr ? -m[16 * (4 * q + g)] : 0.0;
+#pragma unroll
+            for (int i = 0; i < NW; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) acc[i][v] = r0[16 * i + 4 * v];
+            branch_end<0>();
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) fa[q] = -F[(4 * q + g) * S::kLd + 16 * me.row + rr];
+            static_for<NW>([&](auto i) {
+                if (i == ib) {
+                    acc[i] = d4_t{0.0, 0.0, 0.0, 0.0};
+                    branch_end<i>();
+                }
+            });
+        }
+        // the next block column first, so that it is published meanwhile
+        const int next = ib + 1 < end ? ib + 1 : -1;
+        if (next >= 0 && next < NW) {
+            double f[4];
+            load(next, f);
+            static_for<NW>([&](auto i) {
+                if (i == next) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[q], fa[q], acc[i], 0, 0, 0);
+                    publish_col(acc[i], b + 1, rr, g);
+                    branch_end<i>();
+                }
+            });
+        }
+        static_for<NW>([&](auto i) {
+            if (i < end) {
+                if constexpr (i + 1 < NW) load(i + 1, fb[(i + 1) & 1]);
+                if (i != next) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[i & 1][q], fa[q], acc[i], 0, 0, 0);
+                    branch_end<i>();
+                }
+            }
+        });
+        if (own) {
+            static_for<NW>([&](auto i) {
+                if (i == ib) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[i][v] = nw[256 * (b & 1) + 64 * v + lane];
+                    branch_end<i>();
+                }
+            });
+        }
+        if (b + 1 < nblk) publish_row(b + 1);
+        __builtin_amdgcn_s_setprio(0);
+    }
+    if (__syncthreads_or(viol)) return false;
+
+    const int ln = opaque(lane0), row = 16 * me.row + (ln & 15), c = 16 * me.c0 + (ln >> 4);
+#pragma unroll
+    for (int i = 0; i < NW; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int col = c + 16 * i + 4 * v;
+            if (row < L && col < L) static_cast<TO *>(a.out)[row + (int64_t)col * a.ldo] = (TO)acc[i][v];
+        }
+    return true;
+}
+
+template <int N, typename TI, typename TO>
+__device__ __attribute__((always_inline)) inline bool gj_ahead(const LeafArgs &a, double *sm) {
+    using S = AheadLds<N>;
+    const int t = threadIdx.x, lane0 = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int L = a.L;
+    if (L < 1 || L > N) return false;  // the same in every thread
+    constexpr auto kSteps = std::make_integer_sequence<int, 16>{};
+    const int nblk = (L + 15) >> 4;
+
+    // Every role has a loop of its own, with the registers that it needs; all
+    // meet at the same two barriers per block step, and two before the first.
+    if (w == 0) {
+#pragma unroll 1
+        for (int b = -1; b < nblk; ++b) {
+            const int lane = opaque(lane0), rr = lane & 15, g = lane >> 4;
+            const int u = b & 1, n = u ^ 1;
+            double *const mini = sm + S::oMini + 2 * S::kMini * u;
+            wg_barrier();
+            // What the wave reads from here on is not written before the next
+            // block step, so its second barrier may stand anywhere.  Order 64
+            // waits for this wave, which does what it can before; order 128
+            // has time and leaves the SIMD to the panels (2 700 cycles, not
+            // 3 700).
+            if (N == 128) wg_barrier();
+            if (b >= 0 && b + 1 < nblk) {
+                const bool cl = g & 1;
+                double *const x0 = mini + (cl ? S::kMini : 0) + rr;
+                const double *const dr = sm + S::oDr + 256 * u;
+                const double *const r0 = (cl ? sm + S::oDm + 256 * u : dr) + rr;
+                double x[16], r[16];
+#pragma unroll
+                for (int j = 0; j < 16; ++j) {
+                    x[j] = x0[S::kMLd * j];
+                    r[j] = r0[16 * j];
+                }
+                mini_half(x, r, cl ? dr[17 * rr] : 1.0, kSteps);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) x0[S::kMLd * j] = x[j];
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+            if (b + 1 < nblk) {
+                __builtin_amdgcn_s_setprio(3);
+                const double *const pub = sm + S::oPub + 256 * n;
+                double *const nw = sm + S::oNew + 256 * n;
+                d4_t D;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) D[v] = pub[64 * v + lane];
+                if (b >= 0) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+                        D = __builtin_amdgcn_mfma_f64_16x16x4f64(mini[S::kMini + S::kMLd * (4 * q + g) + rr],
+                                                                 -mini[S::kMLd * (4 * q + g) + rr], D, 0, 0, 0);
+                }
+                if (N == 64) wg_barrier();
+                diag_chain(D, lane0, sm + S::oDm + 256 * n, sm + S::oDr + 256 * n, sm + S::oDump, kSteps);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) nw[64 * v + lane] = D[v];
+                __builtin_amdgcn_s_setprio(0);
+            } else if (N == 64) {
+                wg_barrier();
+            }
+        }
+        return !__syncthreads_or(0);
+    }
+    if (w == ahead_checks(N)) {
+        bool viol = false;
+        wg_barrier();
+        wg_barrier();
+#pragma unroll 1
+        for (int b = 0; b < nblk; ++b) {
+            const double *const dr = sm + S::oDr + 256 * (b & 1), *const dm = sm + S::oDm + 256 * (b & 1);
+            wg_barrier();
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int e = lane0 + 64 * q, k = e >> 4, l = e & 15;
+                const double piv = dm[17 * k];
+                viol = viol | !plain_pivot(piv) | ((l > k) & !(fabs(dm[e]) <= fabs(piv)));
+                // block column b's multiplicand
+                sm[S::oR + k * S::kPrLd + N + l] = k >= l ? dr[e] : 0.0;
+            }
+            wg_barrier();
+        }
+        return !__syncthreads_or(viol);
+    }
+    const AheadRole me = ahead_role(N, w);
+    if (N == 128 && w < 8 && w != 4) return ahead_rows<N, 8, TI, TO>(a, sm, me, lane0);
+    return ahead_rows<N, 4, TI, TO>(a, sm, me, lane0);
 }
 
 // ------------------------------------------------- two-workgroup panel ---
@@ -1132,22 +1536,36 @@ __global__ void __launch_bounds__(256) leaf_duo_reset(double *xg, int64_t nd, in
     if (e < ni) xc[e] = -1;
 }
 
+template <int TR, int RR, int RC, bool WHOLE>
+constexpr int gj2d_waves() {
+    return WHOLE ? ahead_waves(TR * RR) : TR / 4;
+}
+
 template <int TR, int RR, int RC, bool WHOLE, typename TI, typename TO>
 __device__ __attribute__((always_inline)) inline void gj2d_any(const LeafArgs &a) {
-    constexpr int NW = TR / 4;                 // waves
+    constexpr int NW = TR / 4;                 // the search's waves
     constexpr int RB = TR * RR / (16 * NW);    // 16-row blocks per wave
     static_assert(RB * 16 * NW == TR * RR && NW * 64 == 16 * TR, "row blocks cover the rows");
-    constexpr int D0 = BlkLds<NW, RB, RC>::kDoubles, D1 = RunLds<TR, RR, RC>::kDoubles;
+    static_assert(!WHOLE || (16 * RC == TR * RR && gj2d_waves<TR, RR, RC, WHOLE>() >= NW), "whole leaves are square");
+    constexpr int D0 = WHOLE ? AheadLds<TR * RR>::kDoubles : BlkLds<NW, RB, RC>::kDoubles;
+    constexpr int D1 = RunLds<TR, RR, RC>::kDoubles;
     __shared__ __attribute__((aligned(16))) double sm[D0 > D1 ? D0 : D1];
     if (a.spec && *a.spec != 0) {
-        if (gj_blocked<NW, RB, RC, WHOLE, TI, TO>(a, sm)) return;
+        bool ok;
+        if constexpr (WHOLE)
+            ok = gj_ahead<TR * RR, TI, TO>(a, sm);
+        else
+            ok = gj_blocked<NW, RB, RC>(a, sm);
+        if (ok) return;
         if (threadIdx.x == 0) *a.spec = 0;
     }
+    // the waves that only the blocked tier has
+    if (WHOLE && threadIdx.x >= 16 * TR) return;
     gj2d_run<TR, RR, RC, WHOLE, TI, TO>(a, sm);
 }
 
 template <int TR, int RR, int RC, bool WHOLE, typename TI, typename TO>
-__global__ void __launch_bounds__(16 * TR) leaf_gj2d(LeafArgs a) {
+__global__ void __launch_bounds__((64 * gj2d_waves<TR, RR, RC, WHOLE>())) leaf_gj2d(LeafArgs a) {
     gj2d_any<TR, RR, RC, WHOLE, TI, TO>(a);
 }
 
@@ -1155,7 +1573,7 @@ __global__ void __launch_bounds__(16 * TR) leaf_gj2d(LeafArgs a) {
 // device code as a single leaf, so every leaf's result is identical to the
 // one it gets when launched alone.
 template <int TR, int RR, int RC, typename TI, typename TO>
-__global__ void __launch_bounds__(16 * TR) leaf_gj2d_batch(LeafBatch b) {
+__global__ void __launch_bounds__((64 * gj2d_waves<TR, RR, RC, true>())) leaf_gj2d_batch(LeafBatch b) {
     const LeafItem &it = b.item[blockIdx.x];
     LeafArgs a{};
     a.in = it.in;
@@ -1369,7 +1787,7 @@ __global__ void __launch_bounds__(256)
 // ---------------------------------------------------------------- launch ---
 template <int TR, int RR, int RC, bool WHOLE, typename TI, typename TO>
 hipError_t gj2d_launch(const LeafArgs &la, hipStream_t s) {
-    hipLaunchKernelGGL((leaf_gj2d<TR, RR, RC, WHOLE, TI, TO>), dim3(1), dim3(16 * TR), 0, s, la);
+    hipLaunchKernelGGL((leaf_gj2d<TR, RR, RC, WHOLE, TI, TO>), dim3(1), dim3(64 * gj2d_waves<TR, RR, RC, WHOLE>()), 0, s, la);
     return hipGetLastError();
 }
 
@@ -1634,19 +2052,19 @@ hipError_t leaf_batch_launch(const LeafItem *items, int count, DType dt, hipStre
     if (small.count) {
         if (dt == kF64)
             hipLaunchKernelGGL((leaf_gj2d_batch<16, 4, 4, double, double>), dim3(small.count),
-                               dim3(256), 0, s, small);
+                               dim3(64 * ahead_waves(64)), 0, s, small);
         else
             hipLaunchKernelGGL((leaf_gj2d_batch<16, 4, 4, float, float>), dim3(small.count),
-                               dim3(256), 0, s, small);
+                               dim3(64 * ahead_waves(64)), 0, s, small);
         e = hipGetLastError();
     }
     if (e == hipSuccess && big.count) {
         if (dt == kF64)
             hipLaunchKernelGGL((leaf_gj2d_batch<kLeaf128TR, 128 / kLeaf128TR, 8, double, double>),
-                               dim3(big.count), dim3(16 * kLeaf128TR), 0, s, big);
+                               dim3(big.count), dim3(64 * ahead_waves(128)), 0, s, big);
         else
             hipLaunchKernelGGL((leaf_gj2d_batch<kLeaf128TR, 128 / kLeaf128TR, 8, float, float>),
-                               dim3(big.count), dim3(16 * kLeaf128TR), 0, s, big);
+                               dim3(big.count), dim3(64 * ahead_waves(128)), 0, s, big);
         e = hipGetLastError();
     }
     if (info) {
