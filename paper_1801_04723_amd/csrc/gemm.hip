@@ -700,31 +700,46 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_bf16(GroupArgs<NG> g) {
 }
 
 // Large products on the BF16 matrix cores: eight waves share a 256 x 256
-// tile (128 x 64 per wave), for products of at least 256 such tiles with
-// 16-byte aligned rows of whole float4 vectors.  A 32-deep slab carries twice
-// the flops per byte of FP32 operands loaded that the 128 x 128 tile does,
-// and each wave issues 32 matrix instructions between two barriers instead
-// of 16, which covers more of the next slab's load latency.  Staging
-// (rounding, swizzled k chunks) and epilogue are gemm_bf16's (plain BF16
-// only: bf16x3 keeps the 128 x 128 tile, whose hi and lo planes fit two
-// workgroups per CU).
-template <int BM, int BN, int WM, int WN, int NG>
+// tile (128 x 64 per wave); 16-byte aligned rows of whole float4 vectors.  A 32-deep slab carries twice
+// the flops per byte of FP32 operands loaded and per rounded operand that the
+// 128 x 128 tile does.  Rounding and epilogue are gemm_bf16's.
+//
+// A CU holds one workgroup, so the waves cover their own latencies: the next
+// slab is rounded and stored piece by piece between the matrix instructions of
+// the current one, from registers loaded an iteration earlier.  Rows have a
+// 64-byte pitch and 16 bytes more per four rows, and the k chunk c of row r
+// lies at ((c ^ -(r / 4)) - r / 4) mod 4: the 16 lanes that a 16-byte read
+// serves together ({0-3, 12-15, 20-23, 24-27} and so on) and 16 stores to
+// rows four apart then fall on different banks.
+//
+// What bounds it: the matrix cores at the rate that this card holds under
+// load; bf16x3 at 8192 x 8192 x 4096 reaches 1 145 TFLOP/s (a library BF16
+// product of order 4096: 1 124).  The 128 x 128 tile was bound by LDS: with an
+// 80-byte pitch its reads took twice the cycles of its matrix instructions.
+// bf16x3 4096^3 488 -> 357 us, 8192 x 8192 x 4096 1 897 -> 1 441 us; plain
+// BF16 (the conversion of twice as many values per matrix instruction shows)
+// 229 -> 209 and 996 -> 915 us against an 80-byte pitch with all conversions
+// after the matrix instructions.
+template <int BM, int BN, int WM, int WN, bool X3, int NG>
 __global__ void __launch_bounds__(512, 1) gemm_bf16_big(GroupArgs<NG> g) {
     constexpr int BK = 32;
     constexpr int NT = 512;
     constexpr int WAVES_M = BM / WM;
     static_assert(WAVES_M * (BN / WN) == 8, "eight waves per workgroup");
     constexpr int TM = WM / 16, TN = WN / 16;
-    constexpr int LDK = BK + 8;            // LDS pitch (elements) of one m or n row
     constexpr int KPA = BM * BK / NT / 4;  // k per thread in the A slab (4 rows each)
     constexpr int TPC = NT / BN;           // threads per column of the B slab
     constexpr int KPB = BK / TPC;          // k per thread in the B slab
-    static_assert(KPA >= 1 && KPB % 8 == 0, "slab/thread mismatch");
+    constexpr int NP = X3 ? 2 : 1;         // hi (and lo) planes
+    static_assert(BM == 256 && KPA == 4 && KPB == 16 && TM == 8, "slab/thread mismatch");
     typedef typename BfVec<KPA>::type va_t;
-    auto swz = [](int row) { return (row >> 4) & 3; };
+    auto at = [](int row, int chunk) {  // element offset of a k chunk
+        const int q = row >> 2;
+        return row * BK + 8 * (q + (((chunk ^ -q) - q) & 3));
+    };
 
-    __shared__ __attribute__((aligned(16))) __bf16 As[2][BM * LDK];
-    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][BN * LDK];
+    __shared__ __attribute__((aligned(16))) __bf16 As[2][NP][BM * BK + 2 * BM];
+    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][NP][BN * BK + 2 * BN];
 
     const int bid = blockIdx.x;
     const int pi = group_member(g, bid);
@@ -740,15 +755,16 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_big(GroupArgs<NG> g) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm0 = (wave % WAVES_M) * WM, wn0 = (wave / WAVES_M) * WN;
 
-    // A slab: rows 4*mq .. 4*mq+3, k = kq*KPA .. kq*KPA + KPA-1
-    const int mq = tid % (BM / 4), kq = tid / (BM / 4);
+    // A slab: rows 4*mq .. 4*mq+3, k = kq*KPA .. kq*KPA + KPA-1; a wave holds
+    // 32 row quads of both halves of a chunk
+    const int mq = (tid & 31) | ((tid >> 1) & 32), kq = ((tid >> 5) & 1) | ((tid >> 7) << 1);
     const int am = m0 + 4 * mq;
     // B slab: column bn, k = bk .. bk + KPB-1
     const int bn = tid / TPC, bk = (tid % TPC) * KPB;
     const int bcol = n0 + bn;
 
     float ra[KPA][4], rb[KPB];
-    auto gload = [&](int k0) {
+    auto load_a = [&](int k0) {
 #pragma unroll
         for (int j = 0; j < KPA; ++j) {
             const int k = k0 + kq * KPA + j;
@@ -759,6 +775,8 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_big(GroupArgs<NG> g) {
             ra[j][2] = ok ? x.z : 0.f;
             ra[j][3] = ok ? x.w : 0.f;
         }
+    };
+    auto load_b = [&](int k0) {
 #pragma unroll
         for (int h = 0; h < KPB / 4; ++h) {
             const int k = k0 + bk + 4 * h;
@@ -770,23 +788,30 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_big(GroupArgs<NG> g) {
             rb[4 * h + 3] = ok ? x.w : 0.f;
         }
     };
-    auto sstore = [&](int buf) {
+    // row i of the thread's four, and its k chunk h
+    auto store_a = [&](int buf, int i) {
+        va_t hi, lo;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            va_t hi;
-#pragma unroll
-            for (int j = 0; j < KPA; ++j) hi[j] = (__bf16)ra[j][i];
-            const int row = 4 * mq + i, k = kq * KPA;
-            *reinterpret_cast<va_t *>(&As[buf][row * LDK + (((k >> 3) ^ swz(row)) << 3) + (k & 7)]) = hi;
+        for (int j = 0; j < KPA; ++j) {
+            const __bf16 h = (__bf16)ra[j][i];
+            hi[j] = h;
+            if (X3) lo[j] = (__bf16)(ra[j][i] - (float)h);
         }
+        const int off = at(4 * mq, kq >> 1) + BK * i + 4 * (kq & 1);
+        *reinterpret_cast<va_t *>(&As[buf][0][off]) = hi;
+        if (X3) *reinterpret_cast<va_t *>(&As[buf][NP - 1][off]) = lo;
+    };
+    auto store_b = [&](int buf, int h) {
+        bf8_t hi, lo;
 #pragma unroll
-        for (int h0 = 0; h0 < KPB; h0 += 8) {
-            bf8_t hi;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) hi[j] = (__bf16)rb[h0 + j];
-            const int k = bk + h0;
-            *reinterpret_cast<bf8_t *>(&Bs[buf][bn * LDK + (((k >> 3) ^ swz(bn)) << 3) + (k & 7)]) = hi;
+        for (int j = 0; j < 8; ++j) {
+            const __bf16 x = (__bf16)rb[8 * h + j];
+            hi[j] = x;
+            if (X3) lo[j] = (__bf16)(rb[8 * h + j] - (float)x);
         }
+        const int off = at(bn, (bk >> 3) + h);
+        *reinterpret_cast<bf8_t *>(&Bs[buf][0][off]) = hi;
+        if (X3) *reinterpret_cast<bf8_t *>(&Bs[buf][NP - 1][off]) = lo;
     };
 
     f4_t acc[TM][TN];
@@ -796,35 +821,56 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_big(GroupArgs<NG> g) {
         for (int j = 0; j < TN; ++j) acc[i][j] = f4_t{0, 0, 0, 0};
 
     const int g4 = lane >> 4, c16 = lane & 15;
-    auto compute = [&](int buf) {
-        bf8_t b[TN];
+    const int oa = at(wm0 + c16, g4), ob = at(wn0 + c16, g4);
+    constexpr int o16 = 16 * BK + 8 * 4;  // 16 rows on
+    // Slab in buffer buf; more: the next slab goes to the other buffer and the
+    // registers are loaded with the one at k2.
+    auto compute = [&](int buf, auto more, int k2) {
+        bf8_t b[NP][TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int row = wn0 + 16 * j + c16;
-            b[j] = *reinterpret_cast<const bf8_t *>(&Bs[buf][row * LDK + ((g4 ^ swz(row)) << 3)]);
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int row = wm0 + 16 * i + c16;
-            const bf8_t a = *reinterpret_cast<const bf8_t *>(&As[buf][row * LDK + ((g4 ^ swz(row)) << 3)]);
+        for (int pl = 0; pl < NP; ++pl)
 #pragma unroll
             for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j], a, acc[i][j], 0, 0, 0);
+                b[pl][j] = *reinterpret_cast<const bf8_t *>(&Bs[buf][pl][ob + o16 * j]);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            bf8_t a[NP];
+#pragma unroll
+            for (int pl = 0; pl < NP; ++pl)
+                a[pl] = *reinterpret_cast<const bf8_t *>(&As[buf][pl][oa + o16 * i]);
+            if constexpr (more) {
+                if (i == 1 || i == 2) store_b(buf ^ 1, i - 1);
+                if (i == 3) load_b(k2);
+                if (i >= 4) store_a(buf ^ 1, i - 4);
+                if (i == TM - 1) load_a(k2);
+            }
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[0][j], a[0], acc[i][j], 0, 0, 0);
+                if (X3) {
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[0][j], a[NP - 1], acc[i][j], 0, 0, 0);
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[NP - 1][j], a[0], acc[i][j], 0, 0, 0);
+                }
+            }
         }
     };
 
     const int KT = (K + BK - 1) / BK;
     if (KT > 0) {
-        gload(0);
-        sstore(0);
+        load_a(0);
+        load_b(0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) store_a(0, i);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) store_b(0, h);
+        load_a(BK);
+        load_b(BK);
         __syncthreads();
         for (int kt = 0; kt + 1 < KT; ++kt) {
-            gload((kt + 1) * BK);
-            compute(kt & 1);
-            sstore((kt & 1) ^ 1);
+            compute(kt & 1, std::true_type{}, (kt + 2) * BK);
             __syncthreads();
         }
-        compute((KT - 1) & 1);
+        compute((KT - 1) & 1, std::false_type{}, 0);
     }
 
     const float *__restrict__ C0 = static_cast<const float *>(P.C0);
@@ -908,12 +954,12 @@ hipError_t launch_bf16_group(const GemmProb *probs, int count, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int BM, int BN, int WM, int WN, int N>
+template <int BM, int BN, int WM, int WN, bool X3, int N>
 hipError_t launch_bf16_big_group(const GemmProb *probs, int count, hipStream_t s) {
     GroupArgs<N> g;
     const int total = make_group<BM, BN, N>(probs, count, g);
     if (total == 0) return hipSuccess;
-    hipLaunchKernelGGL((gemm_bf16_big<BM, BN, WM, WN, N>), dim3(total), dim3(512), 0, s, g);
+    hipLaunchKernelGGL((gemm_bf16_big<BM, BN, WM, WN, X3, N>), dim3(total), dim3(512), 0, s, g);
     return hipGetLastError();
 }
 
@@ -951,10 +997,20 @@ Cfg choose_cfg(const GemmProb &p, DType dt) {
     if (dt == kBF16 || dt == kBF16X3) {
         // float4 loads along m (A) and along k (B)
         c.path = p.m % 4 == 0 && p.k % 4 == 0 && p.lda % 4 == 0 && p.ldb % 4 == 0 && aligned ? kFast : kEdge;
-        // plain BF16: eight-wave 256 x 256 tiles once they alone fill the
-        // GPU; not for the lower-triangle mode
+        // Eight-wave 256 x 256 tiles (one workgroup per CU) where the tiles
+        // fill at least 5/8 of their rounds over the 256 CUs and k covers the
+        // longer prologue; not for the lower-triangle mode.  Against the 128 x
+        // 128 tiles (bf16x3 / bf16): 3584^3 (196 tiles) 433 -> 329 / 295 -> 194
+        // us; 4096^3 (256) 488 -> 357 for bf16x3; 2560 x 4096 x 512
+        // (160) 65 -> 58 / 38.7 -> 38.1; 4864^3 (361) 895 -> 797 / 541 -> 511.
+        // Below the line: 4100 x 4092 x 516 (272) 109 -> 115 / -; 2560 x 4096
+        // x 128 23.7 -> 25.9 / 17.9 -> 21.1.  Plain BF16 also takes them from
+        // 256 tiles on for every k: 4352^3 (289) 428 -> 400, 4096 x 4096 x 64
+        // level.
         const int64_t big = ((p.m + 255) / 256) * ((p.n + 255) / 256);
-        if (dt == kBF16 && c.path == kFast && !p.lower && big >= 256) c.tile = 256;
+        const int64_t rounds = (big + 255) / 256;
+        const bool full = 8 * big >= 5 * 256 * rounds && p.k >= 512;
+        if (c.path == kFast && !p.lower && (full || (dt == kBF16 && big >= 256))) c.tile = 256;
         return c;
     }
     const int bk = fast_bk(c.tile, es);
@@ -985,8 +1041,7 @@ hipError_t launch_cfg(Cfg c, const GemmProb *probs, int count, hipStream_t s) {
 
 template <bool X3, int N>
 hipError_t launch_cfg_bf16(Cfg c, const GemmProb *probs, int count, hipStream_t s) {
-    if constexpr (!X3)
-        if (c.tile == 256) return launch_bf16_big_group<256, 256, 128, 64, N>(probs, count, s);
+    if (c.tile == 256) return launch_bf16_big_group<256, 256, 128, 64, X3, N>(probs, count, s);
     if (c.tile == 128)
         return c.path == kFast ? launch_bf16_group<128, 128, 64, 32, X3, true, N, 8>(probs, count, s)
                       : launch_bf16_group<128, 128, 64, 64, X3, false, N>(probs, count, s);
@@ -1011,7 +1066,7 @@ const char *cfg_name(Cfg c, DType dt) {
         {{"gemm_bf16x3_128x128_edge", "gemm_bf16x3_128x128", ""},
          {"gemm_bf16x3_64x64_edge", "gemm_bf16x3_64x64", ""},
          {"gemm_bf16x3_32x32_edge", "gemm_bf16x3_32x32", ""}}};
-    if (c.tile == 256) return "gemm_bf16_256x256";
+    if (c.tile == 256) return dt == kBF16 ? "gemm_bf16_256x256" : "gemm_bf16x3_256x256";
     const int ti = c.tile == 128 ? 0 : c.tile == 64 ? 1 : 2;
     return names[(int)dt][ti][(int)c.path];
 }
