@@ -494,15 +494,24 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
 // (operands transposed as above, so the result block is D^T).  Operands are
 // rounded to BF16 (round to nearest even) while they are staged into LDS,
 // k-contiguous per m (A) or n (B) row so that each lane fetches its eight k
-// with one 16-byte read; the 80-byte row pitch spreads the 16 rows a
-// quarter-wave reads over all 64 banks, and the four 16-byte k chunks of a
-// row are stored in the order chunk ^ ((row >> 4) & 3), which spreads the
-// stores of lanes 64 or 80 bytes x 4 rows apart over the banks while every
-// 16-row read block keeps one order.  X3 splits every operand into
+// with one 16-byte read (bf_slab).  X3 splits every operand into
 // hi = bf16(x) and lo = bf16(x - hi) (x - hi is exact in FP32) and
 // accumulates hi*hi + lo*hi + hi*lo, about 16 significant bits per operand
 // (the lo*lo term, of relative size 2^-16, is dropped).
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+
+// Element offset of 16-byte k chunk `chunk` (0 .. 3) of a slab's row.  Rows
+// have a 64-byte pitch and 16 bytes more per four rows, and the chunks of a row
+// an order of its quad's: the 16 lanes that a 16-byte read serves together
+// ({0-3, 12-15, 20-23, 24-27} and so on) and stores to rows four apart then
+// fall on different banks.  An 80-byte pitch had two lanes on each bank in
+// every read: on the 128 x 128 tile 3000 x 3001 x 2000 takes 182 us instead of
+// 194 as bf16x3 and 118 instead of 129 as BF16, order 2048 86 (90) and 64 (73).
+__device__ inline int bf_slab(int row, int chunk) {
+    const int q = row >> 2;
+    return row * 32 + 8 * (q + (((chunk ^ -q) - q) & 3));
+}
+constexpr int bf_slab_size(int rows) { return rows * 32 + 2 * rows; }
 
 template <int KN>
 struct BfVec {
@@ -516,7 +525,6 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_bf16(GroupArgs<NG> g) {
     constexpr int WAVES_M = BM / WM;
     static_assert(WAVES_M * (BN / WN) == NW, "NW waves per workgroup");
     constexpr int TM = WM / 16, TN = WN / 16;
-    constexpr int LDK = BK + 8;           // LDS pitch (elements) of one m or n row
     constexpr int KPA = BM * BK / NT / 4;  // k per thread in the A slab (4 rows each)
     constexpr int TPC = NT / BN;           // threads per column of the B slab
     constexpr int KPB = BK / TPC;          // k per thread in the B slab
@@ -524,10 +532,9 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_bf16(GroupArgs<NG> g) {
     static_assert(KPA >= 1 && KPB % 4 == 0, "slab/thread mismatch");
     typedef typename BfVec<KPA>::type va_t;
     static_assert(BK == 32, "four 16-byte k chunks per row");
-    auto swz = [](int row) { return (row >> 4) & 3; };
 
-    __shared__ __attribute__((aligned(16))) __bf16 As[2][NP][BM * LDK];
-    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][NP][BN * LDK];
+    __shared__ __attribute__((aligned(16))) __bf16 As[2][NP][bf_slab_size(BM)];
+    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][NP][bf_slab_size(BN)];
 
     const int bid = blockIdx.x;
     const int pi = group_member(g, bid);
@@ -601,8 +608,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_bf16(GroupArgs<NG> g) {
                 hi[j] = h;
                 if (X3) lo[j] = (__bf16)(ra[j][i] - (float)h);
             }
-            const int row = 4 * mq + i, k = kq * KPA;
-            const int off = row * LDK + (((k >> 3) ^ swz(row)) << 3) + (k & 7);
+            const int k = kq * KPA, off = bf_slab(4 * mq, k >> 3) + BK * i + (k & 7);
             *reinterpret_cast<va_t *>(&As[buf][0][off]) = hi;
             if (X3) *reinterpret_cast<va_t *>(&As[buf][NP - 1][off]) = lo;
         }
@@ -618,7 +624,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_bf16(GroupArgs<NG> g) {
                 if (X3) lo[j] = (__bf16)(rb[h0 + j] - (float)h);
             }
             const int k = bk + h0;
-            const int off = bn * LDK + (((k >> 3) ^ swz(bn)) << 3) + (k & 7);
+            const int off = bf_slab(bn, k >> 3) + (k & 7);
             *reinterpret_cast<bc_t *>(&Bs[buf][0][off]) = hi;
             if (X3) *reinterpret_cast<bc_t *>(&Bs[buf][NP - 1][off]) = lo;
         }
@@ -631,20 +637,18 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_bf16(GroupArgs<NG> g) {
         for (int j = 0; j < TN; ++j) acc[i][j] = f4_t{0, 0, 0, 0};
 
     const int g4 = lane >> 4, c16 = lane & 15;
+    const int oa = bf_slab(wm0 + c16, g4), ob = bf_slab(wn0 + c16, g4);
+    constexpr int o16 = bf_slab_size(16);  // 16 rows on
     auto compute = [&](int buf) {
         bf8_t a[NP][TM], b[NP][TN];
 #pragma unroll
         for (int pl = 0; pl < NP; ++pl) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                const int row = wm0 + 16 * i + c16;
-                a[pl][i] = *reinterpret_cast<const bf8_t *>(&As[buf][pl][row * LDK + ((g4 ^ swz(row)) << 3)]);
-            }
+            for (int i = 0; i < TM; ++i)
+                a[pl][i] = *reinterpret_cast<const bf8_t *>(&As[buf][pl][oa + o16 * i]);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int row = wn0 + 16 * j + c16;
-                b[pl][j] = *reinterpret_cast<const bf8_t *>(&Bs[buf][pl][row * LDK + ((g4 ^ swz(row)) << 3)]);
-            }
+            for (int j = 0; j < TN; ++j)
+                b[pl][j] = *reinterpret_cast<const bf8_t *>(&Bs[buf][pl][ob + o16 * j]);
         }
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -706,11 +710,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_bf16(GroupArgs<NG> g) {
 //
 // A CU holds one workgroup, so the waves cover their own latencies: the next
 // slab is rounded and stored piece by piece between the matrix instructions of
-// the current one, from registers loaded an iteration earlier.  Rows have a
-// 64-byte pitch and 16 bytes more per four rows, and the k chunk c of row r
-// lies at ((c ^ -(r / 4)) - r / 4) mod 4: the 16 lanes that a 16-byte read
-// serves together ({0-3, 12-15, 20-23, 24-27} and so on) and 16 stores to
-// rows four apart then fall on different banks.
+// the current one, from registers loaded an iteration earlier.
 //
 // What bounds it: the matrix cores at the rate that this card holds under
 // load; bf16x3 at 8192 x 8192 x 4096 reaches 1 145 TFLOP/s (a library BF16
@@ -733,13 +733,9 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_big(GroupArgs<NG> g) {
     constexpr int NP = X3 ? 2 : 1;         // hi (and lo) planes
     static_assert(BM == 256 && KPA == 4 && KPB == 16 && TM == 8, "slab/thread mismatch");
     typedef typename BfVec<KPA>::type va_t;
-    auto at = [](int row, int chunk) {  // element offset of a k chunk
-        const int q = row >> 2;
-        return row * BK + 8 * (q + (((chunk ^ -q) - q) & 3));
-    };
 
-    __shared__ __attribute__((aligned(16))) __bf16 As[2][NP][BM * BK + 2 * BM];
-    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][NP][BN * BK + 2 * BN];
+    __shared__ __attribute__((aligned(16))) __bf16 As[2][NP][bf_slab_size(BM)];
+    __shared__ __attribute__((aligned(16))) __bf16 Bs[2][NP][bf_slab_size(BN)];
 
     const int bid = blockIdx.x;
     const int pi = group_member(g, bid);
@@ -797,7 +793,7 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_big(GroupArgs<NG> g) {
             hi[j] = h;
             if (X3) lo[j] = (__bf16)(ra[j][i] - (float)h);
         }
-        const int off = at(4 * mq, kq >> 1) + BK * i + 4 * (kq & 1);
+        const int off = bf_slab(4 * mq, kq >> 1) + BK * i + 4 * (kq & 1);
         *reinterpret_cast<va_t *>(&As[buf][0][off]) = hi;
         if (X3) *reinterpret_cast<va_t *>(&As[buf][NP - 1][off]) = lo;
     };
@@ -809,7 +805,7 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_big(GroupArgs<NG> g) {
             hi[j] = x;
             if (X3) lo[j] = (__bf16)(rb[8 * h + j] - (float)x);
         }
-        const int off = at(bn, (bk >> 3) + h);
+        const int off = bf_slab(bn, (bk >> 3) + h);
         *reinterpret_cast<bf8_t *>(&Bs[buf][0][off]) = hi;
         if (X3) *reinterpret_cast<bf8_t *>(&Bs[buf][NP - 1][off]) = lo;
     };
@@ -821,8 +817,8 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_big(GroupArgs<NG> g) {
         for (int j = 0; j < TN; ++j) acc[i][j] = f4_t{0, 0, 0, 0};
 
     const int g4 = lane >> 4, c16 = lane & 15;
-    const int oa = at(wm0 + c16, g4), ob = at(wn0 + c16, g4);
-    constexpr int o16 = 16 * BK + 8 * 4;  // 16 rows on
+    const int oa = bf_slab(wm0 + c16, g4), ob = bf_slab(wn0 + c16, g4);
+    constexpr int o16 = bf_slab_size(16);  // 16 rows on
     // Slab in buffer buf; more: the next slab goes to the other buffer and the
     // registers are loaded with the one at k2.
     auto compute = [&](int buf, auto more, int k2) {
