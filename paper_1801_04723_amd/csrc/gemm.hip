@@ -25,6 +25,7 @@
 
 #include <type_traits>
 
+#include "leaf_blocks.hpp"
 #include "spin_kernels.hpp"
 
 namespace spin {
@@ -288,6 +289,13 @@ __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
 // 32 x 32 tile.  Eight waves put four on each SIMD (two when a product
 // leaves one workgroup per CU), so more of the slab loads and barriers hide
 // behind other waves' matrix instructions.
+//
+// The 32 x 32 tile is taken where the tiles leave CUs idle, so nothing covers a
+// slab's load: its loads are issued four slabs ahead from k = 256 on (FP64 256
+// x 256 x 256 6.27 -> 6.11 us, 512^3 10.7 -> 10.1, 192 x 320 x 1024 17.4 ->
+// 15.5, 640 x 512 x 2048 50.7 -> 46.5).  Shorter k gains nothing from loads in
+// the loop that are not needed (k = 64 3.5 -> 3.7 us).  A wave's eight
+// dependent 16 x 16 x 4 instructions per slab, 512 cycles, bound it then.
 template <int BM, int BN, int BK, int WM, int WN, typename T, int NG, int NW, bool RAG>
 __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     constexpr int NT = 64 * NW;
@@ -346,21 +354,22 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     }
     const int64_t astep = (int64_t)BK * lda;
 
-    vec_t ra[AV], rb[BV];
+    constexpr int PF = RAG || BM != 32 ? 1 : 4;  // slabs loaded ahead, of at least 2 PF
+    vec_t ra[PF][AV], rb[PF][BV];
     // Rows of A beyond M and columns of B beyond N are loaded from clamped
     // (valid) addresses and not zeroed: they only reach accumulator rows and
     // columns that the epilogue discards, so the loaded values are consumed
     // by the LDS stores alone and the compute phase never waits on them.
-    auto gload = [&]() {
+    auto gload = [&](auto p, bool step = true) {
 #pragma unroll
         for (int i = 0; i < AV; ++i) {
-            ra[i] = *reinterpret_cast<const ld_t *>(pa[i]);
-            pa[i] += astep;
+            ra[p][i] = *reinterpret_cast<const ld_t *>(pa[i]);
+            pa[i] += step ? astep : 0;
         }
 #pragma unroll
         for (int i = 0; i < BV; ++i) {
-            rb[i] = *reinterpret_cast<const ld_t *>(pb[i]);
-            pb[i] += BK;
+            rb[p][i] = *reinterpret_cast<const ld_t *>(pb[i]);
+            pb[i] += step ? BK : 0;
         }
     };
     // the last KR = K mod BK columns of A and rows of B, zeros beyond
@@ -370,20 +379,21 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
         for (int i = 0; i < AV; ++i) {
             const int c = (tid + NT * i) / (BM / VW);
 #pragma unroll
-            for (int e = 0; e < VW; ++e) ra[i][e] = c < KR ? pa[i][e] : T(0);
+            for (int e = 0; e < VW; ++e) ra[0][i][e] = c < KR ? pa[i][e] : T(0);
         }
 #pragma unroll
         for (int i = 0; i < BV; ++i) {
             const int kb = ((tid + NT * i) % (BK / VW)) * VW;
 #pragma unroll
-            for (int e = 0; e < VW; ++e) rb[i][e] = kb + e < KR ? pb[i][e] : T(0);
+            for (int e = 0; e < VW; ++e) rb[0][i][e] = kb + e < KR ? pb[i][e] : T(0);
         }
     };
-    auto sstore = [&](int buf) {
+    constexpr std::integral_constant<int, 0> P0{};
+    auto sstore = [&](int buf, auto p) {
 #pragma unroll
-        for (int i = 0; i < AV; ++i) *reinterpret_cast<ld_t *>(&As[buf][sa[i]]) = ra[i];
+        for (int i = 0; i < AV; ++i) *reinterpret_cast<ld_t *>(&As[buf][sa[i]]) = ra[p][i];
 #pragma unroll
-        for (int i = 0; i < BV; ++i) *reinterpret_cast<vec_t *>(&Bs[buf][sb[i]]) = rb[i];
+        for (int i = 0; i < BV; ++i) *reinterpret_cast<vec_t *>(&Bs[buf][sb[i]]) = rb[p][i];
     };
 
     acc_t acc[TM][TN];
@@ -434,30 +444,48 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
         const int KS = KT + (KR > 0 && (!tri || kend > K / BK));
         auto next = [&](int kt) {
             if (kt < KT)
-                gload();
+                gload(P0);
             else if (kt < KS)
                 gload_tail();
         };
         next(0);
-        sstore(0);
+        sstore(0, P0);
         __syncthreads();
         for (int kt = 0; kt < KS; ++kt) {
             next(kt + 1);
             compute(kt & 1);
-            sstore((kt & 1) ^ 1);
+            sstore((kt & 1) ^ 1, P0);
             __syncthreads();
         }
-    } else if (KT > 0) {
-        gload();
-        sstore(0);
+    } else if (KT > 0 && (PF == 1 || KT < 2 * PF)) {
+        gload(P0);
+        sstore(0, P0);
         __syncthreads();
         for (int kt = 0; kt + 1 < KT; ++kt) {
-            gload();
+            gload(P0);
             compute(kt & 1);
-            sstore((kt & 1) ^ 1);
+            sstore((kt & 1) ^ 1, P0);
             __syncthreads();
         }
         compute((KT - 1) & 1);
+    } else if (KT > 0) {
+        // Slab k lies in register set k mod PF.  Loads beyond the last slab
+        // repeat it: with a condition around them the next store waits for the
+        // newest loads too.
+        static_for<PF>([&](auto p) { gload(p); });
+        sstore(0, P0);
+        __syncthreads();
+        for (int k0 = 0; k0 < KT; k0 += PF) {
+            static_for<PF>([&](auto p) {
+                const int kt = k0 + p;
+                if (kt < KT) {
+                    gload(p, kt + PF + 1 < KT);
+                    compute(kt & 1);
+                    if (kt + 1 < KT) sstore((kt & 1) ^ 1, std::integral_constant<int, (p + 1) % PF>{});
+                    __syncthreads();
+                }
+            });
+        }
     }
 
     const T *__restrict__ C0 = static_cast<const T *>(P.C0);
