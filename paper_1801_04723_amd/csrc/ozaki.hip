@@ -218,7 +218,7 @@ __device__ inline unsigned reduce_sum(int s, int m, unsigned bias, unsigned magi
 // v_mfma_i32_16x16x64_i8), K in 64-byte slabs staged through LDS (two
 // buffers, one barrier per slab).  Output bytes (the sums reduced into
 // [0, m_l)) go to cplanes[l][i + j * mp], four consecutive rows per lane.
-constexpr int kTB = 128, kSK = 64, kPitch = 80;  // 80-byte LDS rows: conflict-free fragment reads
+constexpr int kTB = 128, kSK = 64, kPitch = 80;  // LDS row pitch; two lanes share a bank in fragment reads
 
 __global__ void __launch_bounds__(256, 2) k_gemm_i8(const int8_t *__restrict__ ap, const int8_t *__restrict__ bp,
                                                      uint8_t *__restrict__ cp, int m, int n, int64_t mp,
