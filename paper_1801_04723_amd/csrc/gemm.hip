@@ -295,7 +295,11 @@ __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
 // x 256 x 256 6.27 -> 6.11 us, 512^3 10.7 -> 10.1, 192 x 320 x 1024 17.4 ->
 // 15.5, 640 x 512 x 2048 50.7 -> 46.5).  Shorter k gains nothing from loads in
 // the loop that are not needed (k = 64 3.5 -> 3.7 us).  A wave's eight
-// dependent 16 x 16 x 4 instructions per slab, 512 cycles, bound it then.
+// dependent 16 x 16 x 4 instructions per slab, 512 cycles, bound it then.  The
+// 64 x 64 tile, often one workgroup on a CU, loads two slabs ahead from k = 128
+// on (FP32 1024^3 28.3 -> 25.4 us, 1024 x 960 x 2048 57.5 -> 49.9; FP64 47.4
+// -> 46.8, 1280 x 1024 x 4096 278 -> 258); the 128 x 128 tile has no registers
+// left for it.
 template <int BM, int BN, int BK, int WM, int WN, typename T, int NG, int NW, bool RAG>
 __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     constexpr int NT = 64 * NW;
@@ -354,7 +358,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     }
     const int64_t astep = (int64_t)BK * lda;
 
-    constexpr int PF = RAG || BM != 32 ? 1 : 4;  // slabs loaded ahead, of at least 2 PF
+    constexpr int PF = RAG ? 1 : BM == 32 ? 4 : BM == 64 ? 2 : 1;  // slabs loaded ahead, of at least 2 PF
     vec_t ra[PF][AV], rb[PF][BV];
     // Rows of A beyond M and columns of B beyond N are loaded from clamped
     // (valid) addresses and not zeroed: they only reach accumulator rows and

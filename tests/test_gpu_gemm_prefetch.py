@@ -26,3 +26,9 @@ def test_exact_at_each_slab_count(torch_cuda, mode, m, n, slabs):  # noqa: F811
     S.gemm_cm(m, n, k, -1.0, a, m, b, k, 1.0, c, m, d, m, dtype=mode)
     want = c.cpu().double() - b.cpu().double() @ a.cpu().double()  # |sums| < 2^20
     assert torch.equal(d.cpu().double(), want)
+
+
+@pytest.mark.parametrize("mode", ["fp64", "fp32"])
+@pytest.mark.parametrize("m,n,slabs", [(768, 768, 3), (768, 700, 4), (764, 768, 5), (1024, 512, 6), (512, 1023, 9)])
+def test_exact_on_64_tiles(torch_cuda, mode, m, n, slabs):  # noqa: F811
+    test_exact_at_each_slab_count(torch_cuda, mode, m, n, slabs)
