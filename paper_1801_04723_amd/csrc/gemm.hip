@@ -277,7 +277,7 @@ __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
 // (its neighbours' entries, with the same values), and the last K mod BK
 // columns as one more slab, loaded element by element with zeros beyond K.
 // m = 1537, n = 1001, k = 777 in FP64: 113 us in the guarded kernel above,
-// which loads single elements, 64 us here.
+// which loads single elements, 60 us here.
 //
 // The K slab is split into four contiguous chunks of KQ = BK/4 values, one per
 // lane group q = lane/16, and MFMA step kk consumes k = q*KQ + kk in group q
@@ -299,7 +299,9 @@ __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
 // 64 x 64 tile, often one workgroup on a CU, loads two slabs ahead from k = 128
 // on (FP32 1024^3 28.3 -> 25.4 us, 1024 x 960 x 2048 57.5 -> 49.9; FP64 47.4
 // -> 46.8, 1280 x 1024 x 4096 278 -> 258); the 128 x 128 tile has no registers
-// left for it.
+// left for it.  The ragged forms of both tiles do the same and load the tail
+// slab first, into registers of its own (FP64 1537 x 1001 x 777 63.8 -> 60.2 us,
+// 333 x 200 x 1029 21.3 -> 17.4, 125^3 4.9 -> 4.7).
 template <int BM, int BN, int BK, int WM, int WN, typename T, int NG, int NW, bool RAG>
 __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     constexpr int NT = 64 * NW;
@@ -358,7 +360,9 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     }
     const int64_t astep = (int64_t)BK * lda;
 
-    constexpr int PF = RAG ? 1 : BM == 32 ? 4 : BM == 64 ? 2 : 1;  // slabs loaded ahead, of at least 2 PF
+    constexpr int PF = BM == 32 ? 4 : BM == 64 ? 2 : 1;  // slabs loaded ahead, of at least 2 PF
+    constexpr bool TAIL = RAG && PF > 1;                  // the tail slab has registers of its own
+    vec_t ta[TAIL ? AV : 1], tb[TAIL ? BV : 1];
     vec_t ra[PF][AV], rb[PF][BV];
     // Rows of A beyond M and columns of B beyond N are loaded from clamped
     // (valid) addresses and not zeroed: they only reach accumulator rows and
@@ -378,27 +382,30 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     };
     // the last KR = K mod BK columns of A and rows of B, zeros beyond
     const int KR = RAG ? K % BK : 0;
-    auto gload_tail = [&]() {
+    auto gload_tail = [&](vec_t *xa, vec_t *xb, int slabs) {
 #pragma unroll
         for (int i = 0; i < AV; ++i) {
             const int c = (tid + NT * i) / (BM / VW);
+            const T *p = pa[i] + slabs * astep;
 #pragma unroll
-            for (int e = 0; e < VW; ++e) ra[0][i][e] = c < KR ? pa[i][e] : T(0);
+            for (int e = 0; e < VW; ++e) xa[i][e] = c < KR ? p[e] : T(0);
         }
 #pragma unroll
         for (int i = 0; i < BV; ++i) {
             const int kb = ((tid + NT * i) % (BK / VW)) * VW;
+            const T *p = pb[i] + slabs * BK;
 #pragma unroll
-            for (int e = 0; e < VW; ++e) rb[0][i][e] = kb + e < KR ? pb[i][e] : T(0);
+            for (int e = 0; e < VW; ++e) xb[i][e] = kb + e < KR ? p[e] : T(0);
         }
     };
     constexpr std::integral_constant<int, 0> P0{};
-    auto sstore = [&](int buf, auto p) {
+    auto put = [&](int buf, const vec_t *xa, const vec_t *xb) {
 #pragma unroll
-        for (int i = 0; i < AV; ++i) *reinterpret_cast<ld_t *>(&As[buf][sa[i]]) = ra[p][i];
+        for (int i = 0; i < AV; ++i) *reinterpret_cast<ld_t *>(&As[buf][sa[i]]) = xa[i];
 #pragma unroll
-        for (int i = 0; i < BV; ++i) *reinterpret_cast<vec_t *>(&Bs[buf][sb[i]]) = rb[p][i];
+        for (int i = 0; i < BV; ++i) *reinterpret_cast<vec_t *>(&Bs[buf][sb[i]]) = xb[i];
     };
+    auto sstore = [&](int buf, auto p) { put(buf, ra[p], rb[p]); };
 
     acc_t acc[TM][TN];
 #pragma unroll
@@ -443,14 +450,17 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
         for (int i = 0; i < BV; ++i) pb[i] += kt0 * BK;
         KT -= kt0;
     }
-    if constexpr (RAG) {
-        // a triangular k range that ends before K has no tail slab
-        const int KS = KT + (KR > 0 && (!tri || kend > K / BK));
+    // a triangular k range that ends before K has no tail slab
+    const bool tail = RAG && KR > 0 && (!tri || kend > K / BK);
+    if constexpr (TAIL)
+        if (tail) gload_tail(ta, tb, KT);
+    if constexpr (RAG && !TAIL) {
+        const int KS = KT + tail;
         auto next = [&](int kt) {
             if (kt < KT)
                 gload(P0);
             else if (kt < KS)
-                gload_tail();
+                gload_tail(ra[0], rb[0], 0);
         };
         next(0);
         sstore(0, P0);
@@ -491,6 +501,13 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
             });
         }
     }
+    if constexpr (TAIL)
+        if (tail) {
+            // that buffer was last read two slabs ago, before a barrier
+            put(KT & 1, ta, tb);
+            __syncthreads();
+            compute(KT & 1);
+        }
 
     const T *__restrict__ C0 = static_cast<const T *>(P.C0);
     T *D = static_cast<T *>(P.D);

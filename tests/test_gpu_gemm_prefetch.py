@@ -32,3 +32,19 @@ def test_exact_at_each_slab_count(torch_cuda, mode, m, n, slabs):  # noqa: F811
 @pytest.mark.parametrize("m,n,slabs", [(768, 768, 3), (768, 700, 4), (764, 768, 5), (1024, 512, 6), (512, 1023, 9)])
 def test_exact_on_64_tiles(torch_cuda, mode, m, n, slabs):  # noqa: F811
     test_exact_at_each_slab_count(torch_cuda, mode, m, n, slabs)
+
+
+@pytest.mark.parametrize("mode", ["fp64", "fp32"])
+@pytest.mark.parametrize("m,n,k", [(33, 31, 31), (63, 65, 255), (61, 40, 257), (125, 7, 287), (5, 90, 321),
+                                   (767, 769, 95), (769, 767, 129), (1023, 511, 161), (765, 770, 1)])
+def test_exact_with_a_tail_slab(torch_cuda, mode, m, n, k):  # noqa: F811
+    torch = torch_cuda
+    import paper_1801_04723_amd as S
+    dt = torch.float64 if mode == "fp64" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(k + m)
+    a = torch.randint(-30, 31, (k, m + 1), device="cuda", generator=g).to(dt)
+    b = torch.randint(-30, 31, (n, k + 2), device="cuda", generator=g).to(dt)
+    d = torch.empty(n, m, device="cuda", dtype=dt)
+    S.gemm_cm(m, n, k, 1.0, a, m + 1, b, k + 2, 0.0, None, m, d, m, dtype=mode)
+    want = b.cpu().double()[:, :k] @ a.cpu().double()[:, :m]
+    assert torch.equal(d.cpu().double(), want)
