@@ -297,7 +297,8 @@ __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
 // the loop that are not needed (k = 64 3.5 -> 3.7 us).  A wave's eight
 // dependent 16 x 16 x 4 instructions per slab, 512 cycles, bound it then.  The
 // 64 x 64 tile, often one workgroup on a CU, loads two slabs ahead from k = 128
-// on (FP32 1024^3 28.3 -> 25.4 us, 1024 x 960 x 2048 57.5 -> 49.9; FP64 47.4
+// on in FP32, k = 512 in FP64, where it takes longer over a slab and 2688 x 336
+// x 256 lost 1.3 % (FP32 1024^3 28.3 -> 25.4 us, 1024 x 960 x 2048 57.5 -> 49.9; FP64 47.4
 // -> 46.8, 1280 x 1024 x 4096 278 -> 258); the 128 x 128 tile has no registers
 // left for it.  The ragged forms of both tiles do the same and load the tail
 // slab first, into registers of its own (FP64 1537 x 1001 x 777 63.8 -> 60.2 us,
@@ -360,7 +361,8 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     }
     const int64_t astep = (int64_t)BK * lda;
 
-    constexpr int PF = BM == 32 ? 4 : BM == 64 ? 2 : 1;  // slabs loaded ahead, of at least 2 PF
+    constexpr int PF = BM == 32 ? 4 : BM == 64 ? 2 : 1;  // slabs loaded ahead
+    constexpr int PFMIN = BM == 64 && sizeof(T) == 8 ? 16 : 2 * PF;  // of at least so many
     constexpr bool TAIL = RAG && PF > 1;                  // the tail slab has registers of its own
     vec_t ta[TAIL ? AV : 1], tb[TAIL ? BV : 1];
     vec_t ra[PF][AV], rb[PF][BV];
@@ -471,7 +473,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
             sstore((kt & 1) ^ 1, P0);
             __syncthreads();
         }
-    } else if (KT > 0 && (PF == 1 || KT < 2 * PF)) {
+    } else if (KT > 0 && (PF == 1 || KT < PFMIN)) {
         gload(P0);
         sstore(0, P0);
         __syncthreads();
