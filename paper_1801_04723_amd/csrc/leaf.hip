@@ -13,9 +13,10 @@
 // augmented [A | I] would carry).  With r[k] = pivot row of step k and
 // rinv[r[k]] = k, the inverse is  X[rinv[i]][r[c]] = Z[i][c].
 //
-// Tier 1 (L <= 128): one workgroup holds the whole block in registers,
+// Tier 1 (L <= 128): one workgroup holds the whole block in registers.  With
+//   known pivots it runs in 16-step blocks (gj_ahead); a search has it
 //   cyclically distributed (thread (tr, tc) of a TR x 16 grid owns rows
-//   tr + TR*a and columns tc + 16b).  A step costs two barriers: the owners of
+//   tr + TR*a and columns tc + 16b).  A step then costs two barriers: the owners of
 //   column k publish it to LDS, every wave finds the pivot redundantly (DPP
 //   max, then ballots for the smallest row index), the owners of the pivot
 //   row publish the scaled row, and every thread applies the rank-1 update.
@@ -25,15 +26,15 @@
 //   (E = unit entries at the pivot rows) and the pivot rows Q of the other
 //   columns; those columns are then updated by one grouped matrix-core
 //   product  Z[:, out] += U' * Q.  A final pass writes the permuted result.
-//   Up to order 512 the panel's kernel is the same as for whole leaves (full
-//   panels of leaves of order 129 .. 256: two workgroups, leaf_duo), and an
-//   FP64 leaf is not copied first: the first panel and its product read the
+//   Up to order 512 the panel's kernel runs 16-step blocks too (gj_blocked;
+//   full panels of leaves of order 129 .. 256: two workgroups, leaf_duo) with
+//   the same search, and an FP64 leaf is not copied first: the first panel and its product read the
 //   leaf's input in place.  Above 512 a rotating-slot panel kernel works on narrower panels
 //   and the input is copied into Z.
 //
 // Speculation: every kernel up to order 512 first tries the diagonal pivots
 // in 16-step blocks on the matrix cores, checks each choice exactly and falls
-// back to its search when a check fails (gj2d_any, gj_blocked); the result is
+// back to its search when a check fails (gj2d_any, gj_ahead, gj_blocked); the result is
 // the search's bit for bit either way.
 #include <hip/hip_runtime.h>
 
