@@ -100,6 +100,9 @@ struct LeafArgs {
     // try the speculative elimination first; a failed attempt sets it to 0 so
     // that the later leaves of the same inversion go straight to the search.
     int *spec;
+    // Whole leaves: the leaf is the inversion's only launch and resets the
+    // status block itself, with speculation on (1) or off (2).
+    int reset;
     // Two-workgroup panels: this panel's exchange area (multipliers and
     // inverse pivots of its 64 steps), its verdict and decision words, and
     // the number of polls after which a wait for the other workgroup gives
@@ -1551,7 +1554,17 @@ __device__ __attribute__((always_inline)) inline void gj2d_any(const LeafArgs &a
     constexpr int D0 = WHOLE ? AheadLds<TR * RR>::kDoubles : BlkLds<NW, RB, RC>::kDoubles;
     constexpr int D1 = RunLds<TR, RR, RC>::kDoubles;
     __shared__ __attribute__((aligned(16))) double sm[D0 > D1 ? D0 : D1];
-    if (a.spec && *a.spec != 0) {
+    bool spec;
+    if (WHOLE && a.reset) {
+        spec = a.reset == 1;
+        if (threadIdx.x == 0) {
+            for (int i = 0; i < kStatusWords; ++i) a.status[i] = (i == kStatusSpecWord && !spec) ? 0 : INT_MAX;
+            a.status[kFrobCounterWord] = 0;
+        }
+    } else {
+        spec = a.spec && *a.spec != 0;
+    }
+    if (spec) {
         bool ok;
         if constexpr (WHOLE)
             ok = gj_ahead<TR * RR, TI, TO>(a, sm);
@@ -1865,7 +1878,8 @@ bool leaf_fills_exchange(int64_t L) { return duo_leaf(L); }
 hipError_t leaf_launch(const void *in, DType in_dt, int64_t ldi, void *out, DType out_dt,
                        int64_t ldo, int64_t L64, int64_t col0, int *status, void *scratch,
                        bool exch_filled, hipStream_t s,
-                       void (*trace_cb)(void *, const LaunchInfo &, int), void *trace_ctx) {
+                       void (*trace_cb)(void *, const LaunchInfo &, int), void *trace_ctx, int reset) {
+    if (reset && L64 > 128) return hipErrorInvalidValue;
     if (L64 < 1 || L64 > kLeafMaxOrder) return hipErrorInvalidValue;
     const int L = (int)L64;
     const double Ld = (double)L;
@@ -1884,6 +1898,7 @@ hipError_t leaf_launch(const void *in, DType in_dt, int64_t ldi, void *out, DTyp
         la.col0 = (int)col0;
         la.status = status;
         la.spec = status + kStatusSpecWord;
+        la.reset = reset;
         hipError_t e;
         const char *name = "leaf_gj_regs";
         if (in_dt == kF64 && out_dt == kF64)

@@ -84,11 +84,13 @@ hipError_t gemm_launch(const GemmProb *probs, int count, DType dt, hipStream_t s
 //            for an order with leaf_fills_exchange() true and no other leaf or
 //            kernel has written the scratch since; otherwise (always safe)
 //            a leaf that needs them fills them first
+//   reset : orders up to 128: 1 or 2 when the kernel is to do status_reset's
+//            work first, with speculation on or off
 size_t leaf_scratch_bytes(int64_t L);
 hipError_t leaf_launch(const void *in, DType in_dt, int64_t ldi, void *out, DType out_dt,
                        int64_t ldo, int64_t L, int64_t col0, int *status, void *scratch,
                        bool exch_filled, hipStream_t s,
-                       void (*trace_cb)(void *, const LaunchInfo &, int), void *trace_ctx);
+                       void (*trace_cb)(void *, const LaunchInfo &, int), void *trace_ctx, int reset = 0);
 // True when leaf_launch() for order L leaves the exchange areas filled at its
 // end.  Leaves of other orders leave them as they found them.
 bool leaf_fills_exchange(int64_t L);
