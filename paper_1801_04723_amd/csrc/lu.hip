@@ -33,15 +33,25 @@ namespace {
 // column-at-a-time elimination and two substitution passes in LDS with two
 // barriers per column before: order 128 731 -> 46 us.
 
+// Pivots that are normal numbers with a normal reciprocal, which quotient
+// needs.  Blocks with another one (subnormal, above 2^1022, zero or not
+// finite) divide.
+__device__ inline bool normal_pivot(double p) {
+    const unsigned e = (unsigned)(__double_as_longlong(p) >> 52) & 0x7ffu;
+    return e - 1u <= 2043u;
+}
+
 // The quotient f / p from its rounded reciprocal, with one correction step.
+template <bool DIV>
 __device__ inline double quotient(double f, double p, double pinv) {
+    if constexpr (DIV) return f / p;
     const double q = f * pinv;
     return fma(fma(-q, p, f), pinv, q);
 }
 
 // Step K inside the diagonal block.  dr + 16 K gets row K as the step uses it,
 // dm + 16 K the multipliers with the pivot itself at row K, iv[K] 1 / pivot.
-template <int K>
+template <bool DIV, int K>
 __device__ __attribute__((always_inline)) inline void lu_step(d4_t &D, int rr, int g, double *dm, double *dr,
                                                               double *iv, double *dump) {
     constexpr int V = K / 4, G = K % 4;
@@ -57,7 +67,7 @@ __device__ __attribute__((always_inline)) inline void lu_step(d4_t &D, int rr, i
     double *const pr = (prow ? dr : dump) + g;
 #pragma unroll
     for (int v = 0; v < 4; ++v) pr[16 * K + 4 * v] = D[v];
-    const double m = prow ? pinv : quotient(f, piv, pinv);
+    const double m = prow ? pinv : quotient<DIV>(f, piv, pinv);
     const double below = rr > K ? m : 0.0;  // multiplier left of column K
     if (g == 0) dm[16 * K + rr] = prow ? piv : m;
     if (g == 0 && prow) iv[K] = pinv;
@@ -71,24 +81,24 @@ __device__ __attribute__((always_inline)) inline void lu_step(d4_t &D, int rr, i
     if (g == G) D[V] = rr > K ? -m : m;
 }
 
-template <int... K>
+template <bool DIV, int... K>
 __device__ __attribute__((always_inline)) inline void lu_chain(d4_t &D, int lane, double *dm, double *dr, double *iv,
                                                                double *dump, std::integer_sequence<int, K...>) {
     lane = opaque(lane);
-    (lu_step<K>(D, lane & 15, lane >> 4, dm, dr, iv, dump), ...);
+    (lu_step<DIV, K>(D, lane & 15, lane >> 4, dm, dr, iv, dump), ...);
 }
 
 // The 16 steps on one row of the block column; the lane's group of 16 rows is
 // above or below the diagonal block.  pv, iv: lane l % 16 holds pivot l % 16
 // and its reciprocal.
-template <int... K>
+template <bool DIV, int... K>
 __device__ __attribute__((always_inline)) inline void lu_rows(double (&x)[16], const double *dr, int rr, bool above,
                                                               double pv, double iv, double *F, int ld,
                                                               std::integer_sequence<int, K...>) {
     double r[16] = {(above && rr < K ? 0.0 : dr[16 * K + rr])...};
     (
         [&] {
-            const double m = quotient(x[K], row_bcast<K>(pv), row_bcast<K>(iv));
+            const double m = quotient<DIV>(x[K], row_bcast<K>(pv), row_bcast<K>(iv));
             F[K * ld] = m;
             fmac_rows(x, r[K], m);
             x[K] = above ? m : -m;
@@ -98,9 +108,9 @@ __device__ __attribute__((always_inline)) inline void lu_rows(double (&x)[16], c
 
 // The 16 steps on one column of the block row; the lane's group of 16 columns
 // is left or right of the diagonal block.
-template <int... K>
+template <bool DIV, int... K>
 __device__ __attribute__((always_inline)) inline void lu_cols(double (&y)[16], const double *dm, int rr, bool left,
-                                                              double iv, double *R, int ld,
+                                                              double pv, double iv, double *R, int ld,
                                                               std::integer_sequence<int, K...>) {
     double m[16] = {(rr == K || (left && rr < K) ? 0.0 : dm[16 * K + rr])...};
     (
@@ -108,7 +118,7 @@ __device__ __attribute__((always_inline)) inline void lu_cols(double (&y)[16], c
             const double u = y[K];
             R[K * ld] = u;
             fmac_rows(y, m[K], u);
-            y[K] = left ? u : -(u * row_bcast<K>(iv));
+            y[K] = left ? u : DIV ? -(u / row_bcast<K>(pv)) : -(u * row_bcast<K>(iv));
         }(),
         ...);
 }
@@ -161,7 +171,7 @@ __global__ void __launch_bounds__(64 * N)
     publish(0, 0);
     if (w == 0) {
         D = acc[0];
-        lu_chain(D, lane0, dm, dr, iv, dump, kSteps);
+        lu_chain<false>(D, lane0, dm, dr, iv, dump, kSteps);
     }
 #pragma unroll 1
     for (int b = 0; b < nblk; ++b) {
@@ -169,6 +179,17 @@ __global__ void __launch_bounds__(64 * N)
         const int lane = opaque(lane0), rr = lane & 15, g = lane >> 4;
         double *const pc = sm + S::oPc + u * 16 * S::kFLd, *const pr = sm + S::oPr + u * 16 * S::kPrLd;
         __syncthreads();
+        const bool div = __any(!normal_pivot(dm[17 * rr]));  // the same in every wave
+        if (div) {
+            // the chain again, with divisions
+            __syncthreads();
+            if (w == b) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) D[v] = pr[rr * S::kPrLd + 16 * b + 4 * v + g];
+                lu_chain<true>(D, lane, dm, dr, iv, dump, kSteps);
+            }
+            __syncthreads();
+        }
         // ---- panels: one wave per 64 rows, one per 64 columns ----
         constexpr int CH = (16 * N + 63) / 64;
         if (w < CH) {
@@ -176,7 +197,10 @@ __global__ void __launch_bounds__(64 * N)
             double x[16];
 #pragma unroll
             for (int j = 0; j < 16; ++j) x[j] = pc[j * S::kFLd + row];
-            lu_rows(x, dr, rr, (row >> 4) < b, dm[17 * rr], iv[rr], F + row, S::kFLd, kSteps);
+            if (div)
+                lu_rows<true>(x, dr, rr, (row >> 4) < b, dm[17 * rr], iv[rr], F + row, S::kFLd, kSteps);
+            else
+                lu_rows<false>(x, dr, rr, (row >> 4) < b, dm[17 * rr], iv[rr], F + row, S::kFLd, kSteps);
 #pragma unroll
             for (int j = 0; j < 16; ++j) pc[j * S::kFLd + row] = x[j];
         } else if (w < 2 * CH) {
@@ -184,7 +208,10 @@ __global__ void __launch_bounds__(64 * N)
             double y[16];
 #pragma unroll
             for (int j = 0; j < 16; ++j) y[j] = pr[j * S::kPrLd + col];
-            lu_cols(y, dm, rr, (col >> 4) < b, iv[rr], R + col, S::kRLd, kSteps);
+            if (div)
+                lu_cols<true>(y, dm, rr, (col >> 4) < b, dm[17 * rr], iv[rr], R + col, S::kRLd, kSteps);
+            else
+                lu_cols<false>(y, dm, rr, (col >> 4) < b, dm[17 * rr], iv[rr], R + col, S::kRLd, kSteps);
 #pragma unroll
             for (int j = 0; j < 16; ++j) pr[j * S::kPrLd + col] = y[j];
         }
@@ -236,7 +263,7 @@ __global__ void __launch_bounds__(64 * N)
                         branch_end<c>();
                     }
                 });
-                lu_chain(D, lane, dm, dr, iv, dump, kSteps);
+                lu_chain<false>(D, lane, dm, dr, iv, dump, kSteps);
                 __builtin_amdgcn_s_setprio(0);
             }
             static_for<N>([&](auto c) {
