@@ -920,29 +920,55 @@ __global__ void __launch_bounds__(512, 1) gemm_bf16_big(GroupArgs<NG> g) {
         compute((KT - 1) & 1, std::false_type{}, 0);
     }
 
-    const float *__restrict__ C0 = static_cast<const float *>(P.C0);
+    const float *C0 = static_cast<const float *>(P.C0);
     float *D = static_cast<float *>(P.D);
     float *DT = static_cast<float *>(P.DT);
     const double alpha = P.alpha, beta = P.beta;
     const bool use_c = (beta != 0.0) && (C0 != nullptr);
     const bool add_i = P.add_identity != 0;
+    // C0 comes two row blocks ahead of its use: with no second workgroup on the
+    // CU nothing else covers the loads (C0 may be D, but an element is read and
+    // written by the same lane).
+    float cv[2][TN][4];
+    const int gm0 = m0 + wm0 + c16, gn0 = n0 + wn0 + 4 * g4;
+    const float *const cp = C0 + gm0 + (int64_t)gn0 * P.ldc;
+    auto load_c = [&](int i, float (&x)[TN][4]) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const bool ok = gm0 + 16 * i < M && gn0 + 16 * j + v < N;
+                x[j][v] = *(ok ? cp + 16 * i + (16 * j + v) * P.ldc : C0);
+            }
+    };
+    if (use_c) {
+        load_c(0, cv[0]);
+        load_c(1, cv[1]);
+    }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         const int gm = m0 + wm0 + i * 16 + c16;
+        float val[TN][4];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                double x = alpha * (double)acc[i][j][v];
+                if (use_c) x += beta * (double)cv[i & 1][j][v];
+                if (add_i && gm == n0 + wn0 + j * 16 + 4 * g4 + v) x += 1.0;
+                val[j][v] = (float)x;
+            }
+        if (use_c && i + 2 < TM) load_c(i + 2, cv[i & 1]);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int gn = n0 + wn0 + j * 16 + 4 * g4 + v;
                 if (gm < M && gn < N) {
-                    double val = alpha * (double)acc[i][j][v];
-                    if (use_c) val += beta * (double)C0[gm + (int64_t)gn * P.ldc];
-                    if (add_i && gm == gn) val += 1.0;
-                    D[gm + (int64_t)gn * P.ldd] = (float)val;
-                    if (DT != nullptr) DT[gn + (int64_t)gm * P.lddt] = (float)val;
+                    D[gm + (int64_t)gn * P.ldd] = val[j][v];
+                    if (DT != nullptr) DT[gn + (int64_t)gm * P.lddt] = val[j][v];
                 }
             }
-        }
     }
 }
 
