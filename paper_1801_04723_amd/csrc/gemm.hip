@@ -1070,20 +1070,30 @@ Cfg choose_cfg(const GemmProb &p, DType dt) {
     if (dt == kBF16 || dt == kBF16X3) {
         // float4 loads along m (A) and along k (B)
         c.path = p.m % 4 == 0 && p.k % 4 == 0 && p.lda % 4 == 0 && p.ldb % 4 == 0 && aligned ? kFast : kEdge;
-        // Eight-wave 256 x 256 tiles (one workgroup per CU) where the tiles
-        // fill at least 5/8 of their rounds over the 256 CUs and k covers the
-        // longer prologue; not for the lower-triangle mode.  Against the 128 x
-        // 128 tiles (bf16x3 / bf16): 3584^3 (196 tiles) 433 -> 329 / 295 -> 194
-        // us; 4096^3 (256) 488 -> 357 for bf16x3; 2560 x 4096 x 512
-        // (160) 65 -> 58 / 38.7 -> 38.1; 4864^3 (361) 895 -> 797 / 541 -> 511.
-        // Below the line: 4100 x 4092 x 516 (272) 109 -> 115 / -; 2560 x 4096
-        // x 128 23.7 -> 25.9 / 17.9 -> 21.1.  Plain BF16 also takes them from
-        // 256 tiles on for every k: 4352^3 (289) 428 -> 400, 4096 x 4096 x 64
-        // level.
-        const int64_t big = ((p.m + 255) / 256) * ((p.n + 255) / 256);
+        // Eight-wave 256 x 256 tiles, one workgroup per CU, against 128 x 128
+        // tiles, three per CU (without / with C0, us, 128 -> 256 tiles); not
+        // for the lower-triangle mode.
+        // bf16x3: where they fill at least 5/8 of their rounds over the 256
+        // CUs and k covers the longer prologue: 2560 x 4096 x 512 (160 tiles)
+        // 53 -> 51 / 67 -> 56; 4096^3 467 -> 340 / 478 -> 349; below the line
+        // 4100 x 4092 x 516 (272) 109 -> 115, 2560 x 4096 x 128 23.7 -> 25.9.
+        // With a last round up to half empty the line is k = 1024: 6144 x 6144
+        // (576 tiles) k = 512 146 -> 154 / 213 -> 198, 1024 level / 332 -> 312.
+        // Plain BF16: from 256 tiles on for every k (4352^3 428 -> 400, 4096 x
+        // 4096 x 64 level); with fewer where the 128 x 128 tiles no longer fit
+        // one round of 768 (3584 x 3584 x 512, 784 of them, 48 -> 36 / 67 -> 44;
+        // but 3072 x 4096 x 768, 768 of them, 46 -> 50), and from k = 4096 on,
+        // level at worst (2560 x 4096 205 -> 186 / 214 -> 190, 2048 x 5120 193
+        // -> 194 / 201 -> 200; 1024 x 12288 250 -> 259 with C0, so not for
+        // fewer rows).
+        const int64_t big = (int64_t)((p.m + 255) / 256) * ((p.n + 255) / 256);
         const int64_t rounds = (big + 255) / 256;
-        const bool full = 8 * big >= 5 * 256 * rounds && p.k >= 512;
-        if (c.path == kFast && !p.lower && (full || (dt == kBF16 && big >= 256))) c.tile = 256;
+        const bool filled = 8 * big >= 5 * 256 * rounds;
+        const bool sparse = rounds > 1 && 4 * big <= 3 * 256 * rounds;
+        const bool wide = dt == kBF16X3 ? filled && p.k >= (sparse ? 1024 : 512)
+                                        : big >= 256 || (t128 > 768 && p.k >= 512) ||
+                                              (filled && p.k >= 4096 && p.m >= 2048);
+        if (c.path == kFast && !p.lower && wide) c.tile = 256;
         return c;
     }
     const int bk = fast_bk(c.tile, es);
