@@ -302,7 +302,8 @@ __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
 // -> 46.8, 1280 x 1024 x 4096 278 -> 258); the 128 x 128 tile has no registers
 // left for it.  The ragged forms of both tiles do the same and load the tail
 // slab first, into registers of its own (FP64 1537 x 1001 x 777 63.8 -> 60.2 us,
-// 333 x 200 x 1029 21.3 -> 17.4, 125^3 4.9 -> 4.7).
+// 333 x 200 x 1029 21.3 -> 17.4, 125^3 4.9 -> 4.7), and take only the tail's own
+// steps (1777 x 1650 x 40 15.0 -> 13.0, 1537 x 1001 x 777 60.2 -> 58.7).
 template <int BM, int BN, int BK, int WM, int WN, typename T, int NG, int NW, bool RAG>
 __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     constexpr int NT = 64 * NW;
@@ -401,6 +402,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
         }
     };
     constexpr std::integral_constant<int, 0> P0{};
+    constexpr std::integral_constant<int, KQ> kAll{};
     auto put = [&](int buf, const vec_t *xa, const vec_t *xb) {
 #pragma unroll
         for (int i = 0; i < AV; ++i) *reinterpret_cast<ld_t *>(&As[buf][sa[i]]) = xa[i];
@@ -418,11 +420,12 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     const int q = lane >> 4, c16 = lane & 15;
     // B fragments are fetched one 16-byte vector (VW consecutive k) per
     // column block at a time, which bounds their registers to TN vectors.
-    auto compute = [&](int buf) {
+    auto compute = [&](int buf, auto steps) {
         const T *as = &As[buf][(RAG ? VW : 0) + (q * KQ) * A_LD + wm0 + c16];
         const T *bs = &Bs[buf][(wn0 + c16) * B_LD + q * KQ];
 #pragma unroll
         for (int kc = 0; kc < KQ / VW; ++kc) {
+            if (kc * VW >= steps) break;
             vec_t bv[TN];
 #pragma unroll
             for (int j = 0; j < TN; ++j)
@@ -469,7 +472,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
         __syncthreads();
         for (int kt = 0; kt < KS; ++kt) {
             next(kt + 1);
-            compute(kt & 1);
+            compute(kt & 1, kAll);
             sstore((kt & 1) ^ 1, P0);
             __syncthreads();
         }
@@ -479,11 +482,11 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
         __syncthreads();
         for (int kt = 0; kt + 1 < KT; ++kt) {
             gload(P0);
-            compute(kt & 1);
+            compute(kt & 1, kAll);
             sstore((kt & 1) ^ 1, P0);
             __syncthreads();
         }
-        compute((KT - 1) & 1);
+        compute((KT - 1) & 1, kAll);
     } else if (KT > 0) {
         // Slab k lies in register set k mod PF.  Loads beyond the last slab
         // repeat it: with a condition around them the next store waits for the
@@ -496,7 +499,7 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
                 const int kt = k0 + p;
                 if (kt < KT) {
                     gload(p, kt + PF + 1 < KT);
-                    compute(kt & 1);
+                    compute(kt & 1, kAll);
                     if (kt + 1 < KT) sstore((kt & 1) ^ 1, std::integral_constant<int, (p + 1) % PF>{});
                     __syncthreads();
                 }
@@ -505,10 +508,23 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_fast(GroupArgs<NG> g) {
     }
     if constexpr (TAIL)
         if (tail) {
-            // that buffer was last read two slabs ago, before a barrier
-            put(KT & 1, ta, tb);
+            // Column c lies where lane group c mod 4 finds it in step c / 4, so
+            // that the steps beyond KR are left out.  That buffer was last read
+            // two slabs ago, before a barrier.
+            auto at = [](int c) { return (c & 3) * KQ + (c >> 2); };
+#pragma unroll
+            for (int i = 0; i < AV; ++i) {
+                const int c = (tid + NT * i) / (BM / VW);
+                *reinterpret_cast<ld_t *>(&As[KT & 1][sa[i] + (at(c) - c) * A_LD]) = ta[i];
+            }
+#pragma unroll
+            for (int i = 0; i < BV; ++i) {
+                const int kb = ((tid + NT * i) % (BK / VW)) * VW;
+#pragma unroll
+                for (int e = 0; e < VW; ++e) Bs[KT & 1][sb[i] - kb + at(kb + e)] = tb[i][e];
+            }
             __syncthreads();
-            compute(KT & 1);
+            compute(KT & 1, (KR + 3) / 4);
         }
 
     const T *__restrict__ C0 = static_cast<const T *>(P.C0);

@@ -34,3 +34,29 @@ def test_time_grows_with_the_work(torch_cuda, mode, size, less, beta):  # noqa: 
     _us(torch, mode, *less, beta)
     work = (size[0] * size[1] * size[2]) / (less[0] * less[1] * less[2])
     assert _us(torch, mode, *size, beta) <= 13 / 12 * work * _us(torch, mode, *less, beta)
+
+
+def test_tail_costs_less_than_a_slab(torch_cuda):  # noqa: F811
+    """The last k mod 32 columns of a ragged product: eight of them cost less
+    than the 32 that make k a multiple."""
+    _us(torch_cuda, "fp64", 1777, 1650, 64, 0.0)
+    assert _us(torch_cuda, "fp64", 1777, 1650, 40, 0.0) < _us(torch_cuda, "fp64", 1777, 1650, 64, 0.0)
+
+
+@pytest.mark.parametrize("mode", ["fp64", "fp32"])
+@pytest.mark.parametrize("m,n", [(37, 45), (150, 70), (1030, 777)])
+def test_every_tail_length(torch_cuda, mode, m, n):  # noqa: F811
+    """k = 1 .. 33 and one slab more, against FP64 on the host: an element is a
+    sum of k products of numbers below 6 in chains of roundings, so its error is
+    at most 36 k (k + 4) u."""
+    torch = torch_cuda
+    import paper_1801_04723_amd as S
+    dt, u = (torch.float64, 2.0 ** -53) if mode == "fp64" else (torch.float32, 2.0 ** -24)
+    g = torch.Generator().manual_seed(m)
+    a, b = torch.randn(65, m + 1, generator=g, dtype=dt).clamp(-6, 6), torch.randn(n, 67, generator=g, dtype=dt).clamp(-6, 6)
+    da, db = a.cuda(), b.cuda()
+    for k in (*range(1, 34), 35, 63, 65):
+        d = torch.empty(n, m, dtype=dt, device="cuda")
+        S.gemm_cm(m, n, k, 1.0, da, m + 1, db, 67, 0.0, None, m, d, m, dtype=mode)
+        want = b[:, :k].double() @ a[:k, :m].double()
+        assert float((d.cpu().double() - want).abs().max()) <= 36 * k * (k + 4) * u, k
