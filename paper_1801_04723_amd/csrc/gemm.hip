@@ -1119,6 +1119,16 @@ Cfg choose_cfg(const GemmProb &p, DType dt) {
         c.tile = 32;
     } else {
         c.path = p.k % bk == 0 && p.m % vw == 0 && p.lda % vw == 0 && p.ldb % vw == 0 && aligned ? kFast : kRagged;
+        // A short k leaves the epilogue as most of the work, and two 128 x 128
+        // workgroups on a CU cover less of it than the 64 x 64 tile's more and
+        // smaller ones (the same bits), at any rate when their last round is
+        // nearly empty.  FP32 with C0, 128 -> 64 tiles: 3001 x 3001 x 16 46 ->
+        // 29 us, 3201 x 3201 x 130 72.6 -> 49.1; where neither holds 4095 x
+        // 4095 x 130 without C0 57.4 -> 59.8.
+        const int64_t rounds = (t128 + 511) / 512;
+        if (c.path == kRagged && dt == kF32 && c.tile == 128 &&
+            (p.k <= 96 || (p.k <= 192 && 8 * t128 < 7 * 512 * rounds)))
+            c.tile = 64;
     }
     return c;
 }

@@ -28,6 +28,8 @@ def _us(torch, mode, m, n, k, beta):
 @pytest.mark.parametrize("mode,size,less,beta", [
     # plain BF16 below one round of 256 x 256 tiles
     ("bf16", (2048, 5120, 768), (2048, 4864, 768), 0.0),
+    # ragged FP32 with a short k, where 128 x 128 tiles need a second round
+    ("fp32", (3201, 3201, 100), (2801, 2801, 100), 0.0),
 ])
 def test_time_grows_with_the_work(torch_cuda, mode, size, less, beta):  # noqa: F811
     torch = torch_cuda
