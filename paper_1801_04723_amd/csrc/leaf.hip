@@ -377,12 +377,19 @@ __device__ __attribute__((always_inline)) inline void gj2d_run(const LeafArgs &a
 
 // Pivots whose reciprocal the chain forms without the scaling and fix-up of
 // the FP64 division: for these the division leaves divisor and quotient
-// unscaled, so the bits are the same.  Others (zero and non-finite pivots
-// among them) fail the block's check.
+// unscaled, so the bits are the same.  A block whose diagonal says that it has
+// others (far_entry) divides in the chain; where such a pivot comes up without
+// that the block's check fails.
+__device__ inline unsigned exponent_bits(double x) { return (unsigned)(__double_as_longlong(x) >> 52) & 0x7ffu; }
 __device__ inline bool plain_pivot(double x) {
-    const unsigned e = (unsigned)(__double_as_longlong(x) >> 52) & 0x7ffu;
-    return e - 523u <= 1000u;  // |x| in 2^-500 .. 2^501
+    return exponent_bits(x) - 523u <= 1000u;  // |x| in 2^-500 .. 2^501
 }
+__device__ inline bool usable_pivot(double x) { return x != 0.0 && fabs(x) <= DBL_MAX; }
+__device__ inline bool pivot_fails(double x, bool div) { return !(div ? usable_pivot(x) : plain_pivot(x)); }
+// A diagonal entry from which the pivot is not expected within plain_pivot's
+// range, since a matrix that needs no row exchanges keeps its pivots near its
+// diagonal.
+__device__ inline bool far_entry(double x) { return usable_pivot(x) && exponent_bits(x) - 623u > 800u; }
 
 // Step K of the 16 x 16 diagonal block: lane l holds row l % 16 of columns
 // 4 v + l / 16.
@@ -397,7 +404,7 @@ __device__ inline bool plain_pivot(double x) {
 // A lone wave issues an instruction about every five to nine cycles, so the
 // step has no branch: lanes whose store is not wanted store to a dump area.
 // The step's stores go to dm + 16 K + (row) and dr + 16 K + (column).
-template <int K>
+template <bool DIV, int K>
 __device__ __attribute__((always_inline)) inline void diag_step(d4_t &D, int rr, int g, double *dm, double *dr,
                                                                 double *dump) {
     constexpr int V = K / 4, G = K % 4;
@@ -411,10 +418,15 @@ __device__ __attribute__((always_inline)) inline void diag_step(d4_t &D, int rr,
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     double f = dm[16 * K + rr];
     __builtin_amdgcn_sched_barrier(0);  // the read goes out before the arithmetic
-    double y = __builtin_amdgcn_rcp(x);
-    y = fma(y, fma(-x, y, 1.0), y);
-    y = fma(y, fma(-x, y, 1.0), y);
-    y = fma(fma(-x, y, 1.0), y, y);
+    double y;
+    if constexpr (DIV) {
+        y = 1.0 / x;
+    } else {
+        y = __builtin_amdgcn_rcp(x);
+        y = fma(y, fma(-x, y, 1.0), y);
+        y = fma(y, fma(-x, y, 1.0), y);
+        y = fma(fma(-x, y, 1.0), y, y);
+    }
     const double pinv = readlane_f64(y, 16 * G + K);
     const bool prow = rr == K;
     const double unit = prow ? 1.0 : 0.0;
@@ -437,11 +449,20 @@ __device__ __attribute__((always_inline)) inline void diag_step(d4_t &D, int rr,
         : "v"(f), "n"(K));
 }
 
-template <int... K>
-__device__ __attribute__((always_inline)) inline void diag_chain(d4_t &D, int lane, double *dm, double *dr,
+template <bool DIV, int... K>
+__device__ __attribute__((always_inline)) inline void diag_steps(d4_t &D, int lane, double *dm, double *dr,
                                                                  double *dump, std::integer_sequence<int, K...>) {
     lane = opaque(lane);
-    (diag_step<K>(D, lane & 15, lane >> 4, dm, dr, dump), ...);
+    (diag_step<DIV, K>(D, lane & 15, lane >> 4, dm, dr, dump), ...);
+    branch_end<DIV>();
+}
+__device__ __attribute__((always_inline)) inline void diag_chain(bool div, d4_t &D, int lane, double *dm, double *dr,
+                                                                 double *dump) {
+    constexpr auto kSteps = std::make_integer_sequence<int, 16>{};
+    if (div)
+        diag_steps<true>(D, lane, dm, dr, dump, kSteps);
+    else
+        diag_steps<false>(D, lane, dm, dr, dump, kSteps);
 }
 
 // The 16 steps on one row of the block column (x: its 16 columns): F gets the
@@ -465,9 +486,10 @@ __device__ __attribute__((always_inline)) inline bool row_steps(double (&x)[16],
 }
 
 // The 16 steps on one column of the block row (y: its 16 rows): R gets the
-// scaled pivot rows' entries (pitch ld).
+// scaled pivot rows' entries (pitch ld).  Returns whether one is not finite,
+// which every later one then is not either.
 template <int... K>
-__device__ __attribute__((always_inline)) inline void col_steps(double (&y)[16], const double *dm16, double id,
+__device__ __attribute__((always_inline)) inline bool col_steps(double (&y)[16], const double *dm16, double id,
                                                                 double *R, int ld, std::integer_sequence<int, K...>) {
     double m[16] = {dm16[16 * K]...};
     (
@@ -478,6 +500,7 @@ __device__ __attribute__((always_inline)) inline void col_steps(double (&y)[16],
             y[K] = r + 0.0;
         }(),
         ...);
+    return !(fabs(y[15]) <= DBL_MAX);
 }
 
 template <int NW, int RB, int NC>
@@ -519,6 +542,9 @@ __device__ __attribute__((always_inline)) inline bool gj_blocked(const LeafArgs 
             qv[q] = (lane < nb && j < nout) ? src[(k0 + lane) + (int64_t)gj * lds] : 0.0;
         }
     }
+    // the same in every wave (up to 64 columns)
+    static_assert(S::kCols <= 64, "one diagonal entry per lane");
+    const bool div = __any(far_entry(lane < nb ? src[(k0 + lane) * (lds + 1)] : 1.0)) != 0;
     bool viol = false;
     if (k0 > 0) {
         // the rows before the panel must be the used ones and no other
@@ -566,7 +592,7 @@ __device__ __attribute__((always_inline)) inline bool gj_blocked(const LeafArgs 
                 branch_end<i>();
             }
         });
-        diag_chain(D, lane, dm, dr, dump, kSteps);
+        diag_chain(div, D, lane, dm, dr, dump);
     }
 #pragma unroll 1
     for (int b = 0; b < nblk; ++b) {
@@ -592,7 +618,7 @@ __device__ __attribute__((always_inline)) inline bool gj_blocked(const LeafArgs 
                 const int col = 64 * (tk - RCH) + lane;
 #pragma unroll
                 for (int j = 0; j < 16; ++j) x[j] = pr[j * S::kPrLd + col];
-                col_steps(x, dm + rr, dr[17 * rr], R + col, S::kRLd, kSteps);
+                viol = viol | col_steps(x, dm + rr, dr[17 * rr], R + col, S::kRLd, kSteps);
 #pragma unroll
                 for (int j = 0; j < 16; ++j) pr[j * S::kPrLd + col] = x[j];
             }
@@ -603,7 +629,8 @@ __device__ __attribute__((always_inline)) inline bool gj_blocked(const LeafArgs 
             for (int q = 0; q < 4; ++q) {
                 const int e = lane + 64 * q, k = e >> 4, l = e & 15;
                 const double piv = dm[17 * k];
-                viol = viol | !plain_pivot(piv) | ((l > k) & !(fabs(dm[e]) <= fabs(piv)));
+                viol = viol | pivot_fails(piv, div) | ((l > k) & !(fabs(dm[e]) <= fabs(piv))) |
+                       !(fabs(dr[e]) <= DBL_MAX);
             }
         }
         __syncthreads();
@@ -662,7 +689,7 @@ __device__ __attribute__((always_inline)) inline bool gj_blocked(const LeafArgs 
                     });
                 }
             });
-            diag_chain(D, lane, dm, dr, dump, kSteps);
+            diag_chain(div, D, lane, dm, dr, dump);
             __builtin_amdgcn_s_setprio(0);
         }
         static_for<NC>([&](auto c) {
@@ -842,6 +869,7 @@ __device__ __attribute__((always_inline)) inline bool col_half(double (&y)[16], 
             R[K * ld] = r;
             start[K * ld] = r + 0.0;
             half_step<K>(y, m[K], r);
+            if constexpr (K == 15) y[15] = r;
         }(),
         ...);
     return !(fabs(y[15]) <= DBL_MAX);
@@ -1060,9 +1088,18 @@ __device__ __attribute__((always_inline)) inline bool gj_ahead(const LeafArgs &a
     constexpr auto kSteps = std::make_integer_sequence<int, 16>{};
     const int nblk = (L + 15) >> 4;
 
+    // for the two waves that need it
+    auto divide = [&] {
+        bool far = false;
+#pragma unroll
+        for (int i = lane0; i < N; i += 64)
+            far = far | far_entry(i < L ? (double)static_cast<const TI *>(a.in)[i * (a.ldi + 1)] : 1.0);
+        return __any(far) != 0;
+    };
     // Every role has a loop of its own, with the registers that it needs; all
     // meet at the same two barriers per block step, and two before the first.
     if (w == 0) {
+        const bool dv = divide();
 #pragma unroll 1
         for (int b = -1; b < nblk; ++b) {
             const int lane = opaque(lane0), rr = lane & 15, g = lane >> 4;
@@ -1107,7 +1144,7 @@ __device__ __attribute__((always_inline)) inline bool gj_ahead(const LeafArgs &a
                                                                  -mini[S::kMLd * (4 * q + g) + rr], D, 0, 0, 0);
                 }
                 if (N == 64) wg_barrier();
-                diag_chain(D, lane0, sm + S::oDm + 256 * n, sm + S::oDr + 256 * n, sm + S::oDump, kSteps);
+                diag_chain(dv, D, lane0, sm + S::oDm + 256 * n, sm + S::oDr + 256 * n, sm + S::oDump);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) nw[64 * v + lane] = D[v];
                 __builtin_amdgcn_s_setprio(0);
@@ -1118,6 +1155,7 @@ __device__ __attribute__((always_inline)) inline bool gj_ahead(const LeafArgs &a
         return !__syncthreads_or(0);
     }
     if (w == ahead_checks(N)) {
+        const bool dv = divide();
         bool viol = false;
         wg_barrier();
         wg_barrier();
@@ -1129,9 +1167,11 @@ __device__ __attribute__((always_inline)) inline bool gj_ahead(const LeafArgs &a
             for (int q = 0; q < 4; ++q) {
                 const int e = lane0 + 64 * q, k = e >> 4, l = e & 15;
                 const double piv = dm[17 * k];
-                viol = viol | !plain_pivot(piv) | ((l > k) & !(fabs(dm[e]) <= fabs(piv)));
+                const double r = dr[e];
+                viol = viol | pivot_fails(piv, dv) | ((l > k) & !(fabs(dm[e]) <= fabs(piv))) |
+                       !(fabs(r) <= DBL_MAX);
                 // block column b's multiplicand
-                sm[S::oR + k * S::kPrLd + N + l] = k >= l ? dr[e] : 0.0;
+                sm[S::oR + k * S::kPrLd + N + l] = k >= l ? r : 0.0;
             }
             wg_barrier();
         }
