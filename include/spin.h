@@ -31,8 +31,8 @@
  *   Graphs     the second inversion with a given entry point, mode, order,
  *              leading dimensions, buffers and stream workspace records its
  *              launch sequence as a HIP graph and later identical calls replay
- *              it; the first one, and schedules of a few steps, launch their
- *              kernels directly.  At most 64 graphs are kept (the cache is
+ *              it; the first one, and calls of fewer than ten launches, launch
+ *              their kernels directly.  At most 64 graphs are kept (the cache is
  *              emptied when full, after waiting for the device).  The
  *              environment variable SPIN_NO_GRAPH=1 makes every call launch
  *              its kernels directly.

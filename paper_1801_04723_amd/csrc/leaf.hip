@@ -1915,6 +1915,14 @@ size_t leaf_scratch_bytes(int64_t L) {
 
 bool leaf_fills_exchange(int64_t L) { return duo_leaf(L); }
 
+int64_t leaf_launches(int64_t L, DType in_dt) {
+    if (L <= 128) return 1;
+    // panel and product, from order 513 on with a gather between; the exchange
+    // areas' fill or the copy into Z before, the permutation after
+    const int64_t panels = (L + panel_width(L) - 1) / panel_width(L);
+    return panels * (L <= 512 ? 2 : 3) + (duo_leaf(L) ? 1 : 0) + (L <= 512 && in_dt == kF64 ? 0 : 1) + 1;
+}
+
 hipError_t leaf_launch(const void *in, DType in_dt, int64_t ldi, void *out, DType out_dt,
                        int64_t ldo, int64_t L64, int64_t col0, int *status, void *scratch,
                        bool exch_filled, hipStream_t s,

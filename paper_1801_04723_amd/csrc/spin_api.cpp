@@ -433,9 +433,8 @@ struct Workspace {
 };
 
 std::map<hipStream_t, Workspace> g_ws;
-std::map<std::tuple<int, int64_t, int64_t, int64_t, int64_t, const void *, void *, void *, int>,
-         hipGraphExec_t>
-    g_graphs;
+using GraphKey = std::tuple<int, int64_t, int64_t, int64_t, int64_t, const void *, void *, void *, int>;
+std::map<GraphKey, hipGraphExec_t> g_graphs;
 hipStream_t g_capture = nullptr;
 // Largest number of cached graphs (one per mode, shape, buffer set and stream
 // workspace) before the cache is emptied.
@@ -617,24 +616,42 @@ int hip_fail(hipError_t e) {
     return e == hipErrorOutOfMemory ? SPIN_E_NOMEM : SPIN_E_HIP;
 }
 
-// Schedule steps below which a call is never captured: hipGraphLaunch costs the
-// host about 15 us, a plain launch 3 to 5 us, and the first kernel of a graph
-// starts about 10 us later (one order-64 leaf, two launches: 20 us a call in a
-// row and 36 us alone launched directly, 28 and 47 us as a graph; order 256 at
-// leaf 64, 16 steps: 134 us both ways, and 21 us less host time as a graph).
-constexpr size_t kGraphMinSteps = 8;
+// Launches below which a call is never captured: hipGraphLaunch costs the host
+// about 30 us however many it replays, a plain launch 3 to 5 us, and the first
+// kernel of a graph starts about 10 us later.  Direct -> graph, us in a row /
+// alone / of host time: order 128 at leaf 64 (7 launches) 51 -> 56 / 67 -> 70 /
+// 23 -> 33; a leaf of order 192 (9) 108 -> 112 / 130 -> 126 / 41 -> 31; of 256
+// (11) 146 -> 149 / 169 -> 163 / 57 -> 32; of 512 (18) 548 -> 547 / 571 -> 561 /
+// 83 -> 34; mixed FP32, order 64, one step (11) 64 -> 69 / 86 -> 83 / 51 -> 31,
+// two INT8 steps (44) 267 -> 259 / 300 -> 274 / 179 -> 47.
+constexpr int64_t kGraphMinLaunches = 10;
 
-// Enqueue `body(stream)` either directly or through a cached graph.  A key's
-// first call is launched directly and only remembered (an entry without a
-// graph): capture and instantiation cost 1 to 3 us per launch (order 2048 at
-// leaf 128: 1.64 ms for a first call with capture, 1.46 ms without), which a
-// caller with new buffers on every call would never get back.  The second
-// call with the same key captures.  On a stream that is itself being captured
-// the graph is launched as before.
+// Launches of run_plan (a pair of products of different kernels counts as one).
+int64_t plan_launches(const Plan &P, DType dt) {
+    int64_t c = 0;
+    bool filled = false;
+    for (size_t i = 0; i < P.ops.size(); ++i) {
+        if (P.ops[i].kind == 1) {
+            const int64_t L = P.ops[i].L;
+            c += leaf_launches(L, dt) - (filled && leaf_fills_exchange(L) ? 1 : 0);
+            filled = filled || leaf_fills_exchange(L);
+        } else {
+            ++c;
+            if (fold_kind(P, i)) ++i;
+        }
+    }
+    return c;
+}
+
+// Enqueue `body(stream)`, of so many launches, either directly or through a
+// cached graph.  A key's first call is launched directly and only remembered
+// (an entry without a graph): capture and instantiation cost 1 to 3 us per launch (order 2048 at leaf 128:
+// 1.64 ms for a first call with capture, 1.46 ms without), which a caller with
+// new buffers on every call would never get back.  The second call with the
+// same key captures.  On a stream that is itself being captured the graph is
+// launched as before.
 template <typename F>
-int run_maybe_graph(const std::tuple<int, int64_t, int64_t, int64_t, int64_t, const void *, void *,
-                                     void *, int> &key,
-                    hipStream_t s, size_t steps, F body) {
+int run_maybe_graph(const GraphKey &key, hipStream_t s, int64_t launches, F body) {
     auto direct = [&]() -> int {
         hipError_t e = body(s);
         return e == hipSuccess ? SPIN_OK : hip_fail(e);
@@ -643,7 +660,7 @@ int run_maybe_graph(const std::tuple<int, int64_t, int64_t, int64_t, int64_t, co
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
     const bool capturing = cap != hipStreamCaptureStatusNone;
-    if (steps < kGraphMinSteps && !capturing) return direct();
+    if (launches < kGraphMinLaunches && !capturing) return direct();
     auto it = g_graphs.find(key);
     if (it == g_graphs.end() && g_graphs.size() >= kMaxGraphs) {
         // bounded cache: callers that cycle through many buffers must not grow
@@ -742,7 +759,7 @@ int spin_invert(const double *A, int64_t n, int64_t lda, double *Ainv, int64_t l
     };
     return run_maybe_graph(std::make_tuple(spec ? 0 : kNoSpecKey, n, lda, ldx, leaf, (const void *)A, (void *)Ainv,
                                            (void *)w->base, 0),
-                           s, P.ops.size(), body);
+                           s, 1 + plan_launches(P, kF64), body);
 }
 
 int spin_invert_spd(const double *A, int64_t n, int64_t lda, double *Ainv, int64_t ldx,
@@ -767,7 +784,7 @@ int spin_invert_spd(const double *A, int64_t n, int64_t lda, double *Ainv, int64
     };
     return run_maybe_graph(std::make_tuple(spec ? 2 : 2 + kNoSpecKey, n, lda, ldx, leaf, (const void *)A, (void *)Ainv,
                                            (void *)w->base, 0),
-                           s, P.ops.size(), body);
+                           s, 1 + plan_launches(P, kF64), body);
 }
 
 int spin_invert_lu(const double *A, int64_t n, int64_t lda, double *Ainv, int64_t ldx,
@@ -794,7 +811,7 @@ int spin_invert_lu(const double *A, int64_t n, int64_t lda, double *Ainv, int64_
     };
     return run_maybe_graph(std::make_tuple(spec ? 3 : 3 + kNoSpecKey, n, lda, ldx, leaf, (const void *)A, (void *)Ainv,
                                            (void *)w->base, 0),
-                           s, P.ops.size(), body);
+                           s, 1 + plan_launches(P, kF64), body);
 }
 
 int spin_invert_mixed(const double *A, int64_t n, int64_t lda, double *Ainv, int64_t ldx,
@@ -899,9 +916,11 @@ int spin_invert_mixed(const double *A, int64_t n, int64_t lda, double *Ainv, int
         }
         return hipSuccess;
     };
+    const int64_t product = emu ? kOzakiLaunches : 1;
+    const int64_t launches = 3 + plan_launches(P, kF32) + ns_steps * (2 * product + 1) + (ns_steps > 0 ? product + 3 : 0);
     rc = run_maybe_graph(std::make_tuple(1 + 16 * mode + (spec ? 0 : kNoSpecKey), n, lda, ldx, leaf, (const void *)A,
                                          (void *)Ainv, (void *)base, ns_steps),
-                         s, P.ops.size(), body);
+                         s, launches, body);
     if (rc || !rep) return rc;
 
     // Report: residual of the unrefined and of the final inverse.  With

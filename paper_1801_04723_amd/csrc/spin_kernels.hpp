@@ -91,6 +91,9 @@ hipError_t leaf_launch(const void *in, DType in_dt, int64_t ldi, void *out, DTyp
                        int64_t ldo, int64_t L, int64_t col0, int *status, void *scratch,
                        bool exch_filled, hipStream_t s,
                        void (*trace_cb)(void *, const LaunchInfo &, int), void *trace_ctx, int reset = 0);
+// Kernels that leaf_launch() launches for order L (with its exchange areas not
+// yet filled).
+int64_t leaf_launches(int64_t L, DType in_dt);
 // True when leaf_launch() for order L leaves the exchange areas filled at its
 // end.  Leaves of other orders leave them as they found them.
 bool leaf_fills_exchange(int64_t L);
@@ -196,6 +199,7 @@ double ozaki_log2_modulus(int count);
 int ozaki_beta(int count, int64_t k);
 size_t ozaki_workspace_bytes(int64_t m, int64_t n, int64_t k, int count);
 hipError_t ozaki_product(const OzakiProb &p, void *ws, hipStream_t s);
+constexpr int kOzakiLaunches = 7;  // kernels of one such product
 
 // Sum of squares of an (m x n) FP64 view, deterministic: partials (>=
 // frob_partials_count(m, n) doubles behind the counter at kFrobCounterWord of
