@@ -33,7 +33,8 @@
  *              launch sequence as a HIP graph and later identical calls replay
  *              it; the first one, and calls of fewer than ten launches, launch
  *              their kernels directly.  At most 64 graphs are kept (the cache is
- *              emptied when full, after waiting for the device).  The
+ *              emptied when full, after waiting for the device) and 64 first
+ *              calls remembered.  The
  *              environment variable SPIN_NO_GRAPH=1 makes every call launch
  *              its kernels directly.
  *   Leaves     two further environment variables change how a leaf is

@@ -27,6 +27,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <set>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -435,6 +436,9 @@ struct Workspace {
 std::map<hipStream_t, Workspace> g_ws;
 using GraphKey = std::tuple<int, int64_t, int64_t, int64_t, int64_t, const void *, void *, void *, int>;
 std::map<GraphKey, hipGraphExec_t> g_graphs;
+// Keys called once and not yet captured; apart from the graphs, so that neither
+// displaces the other.  At most kMaxGraphs.
+std::set<GraphKey> g_seen;
 hipStream_t g_capture = nullptr;
 // Largest number of cached graphs (one per mode, shape, buffer set and stream
 // workspace) before the cache is emptied.
@@ -446,12 +450,13 @@ constexpr int kNoSpecKey = 1 << 12;
 void drop_graphs_for(void *base) {
     for (auto it = g_graphs.begin(); it != g_graphs.end();) {
         if (std::get<7>(it->first) == base) {
-            if (it->second) hipGraphExecDestroy(it->second);
+            hipGraphExecDestroy(it->second);
             it = g_graphs.erase(it);
         } else {
             ++it;
         }
     }
+    for (auto it = g_seen.begin(); it != g_seen.end();) it = std::get<7>(*it) == base ? g_seen.erase(it) : std::next(it);
 }
 
 // Returns the stream's workspace with at least `bytes` (caller holds g_mu).
@@ -644,8 +649,8 @@ int64_t plan_launches(const Plan &P, DType dt) {
 }
 
 // Enqueue `body(stream)`, of so many launches, either directly or through a
-// cached graph.  A key's first call is launched directly and only remembered
-// (an entry without a graph): capture and instantiation cost 1 to 3 us per launch (order 2048 at leaf 128:
+// cached graph.  A key's first call is launched directly and only remembered:
+// capture and instantiation cost 1 to 3 us per launch (order 2048 at leaf 128:
 // 1.64 ms for a first call with capture, 1.46 ms without), which a caller with
 // new buffers on every call would never get back.  The second call with the
 // same key captures.  On a stream that is itself being captured the graph is
@@ -662,24 +667,23 @@ int run_maybe_graph(const GraphKey &key, hipStream_t s, int64_t launches, F body
     const bool capturing = cap != hipStreamCaptureStatusNone;
     if (launches < kGraphMinLaunches && !capturing) return direct();
     auto it = g_graphs.find(key);
-    if (it == g_graphs.end() && g_graphs.size() >= kMaxGraphs) {
-        // bounded cache: callers that cycle through many buffers must not grow
-        // it without limit.  Entries without a graph go first; otherwise wait
-        // for every launch, then drop all graphs; they are captured again on
-        // their next uses.
-        for (auto e = g_graphs.begin(); e != g_graphs.end();) e = e->second ? std::next(e) : g_graphs.erase(e);
+    if (it == g_graphs.end() && !capturing && !g_seen.erase(key)) {
+        const int rc = direct();
+        if (rc == SPIN_OK) {
+            if (g_seen.size() >= kMaxGraphs) g_seen.clear();
+            g_seen.insert(key);
+        }
+        return rc;
+    }
+    if (it == g_graphs.end()) {
         if (g_graphs.size() >= kMaxGraphs) {
+            // bounded cache: callers that cycle through many buffers must not
+            // grow it without limit.  Wait for every launch, then drop all
+            // graphs; they are captured again on their next uses.
             if (hipDeviceSynchronize() != hipSuccess) return hip_fail(hipErrorUnknown);
             for (auto &kv : g_graphs) hipGraphExecDestroy(kv.second);
             g_graphs.clear();
         }
-    }
-    if (it == g_graphs.end() && !capturing) {
-        const int rc = direct();
-        if (rc == SPIN_OK) g_graphs.emplace(key, nullptr);
-        return rc;
-    }
-    if (it == g_graphs.end() || !it->second) {
         if (!g_capture && hipStreamCreateWithFlags(&g_capture, hipStreamNonBlocking) != hipSuccess)
             return hip_fail(hipErrorUnknown);
         if (hipStreamBeginCapture(g_capture, hipStreamCaptureModeThreadLocal) != hipSuccess)
@@ -695,7 +699,7 @@ int run_maybe_graph(const GraphKey &key, hipStream_t s, int64_t launches, F body
         e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
         hipGraphDestroy(graph);
         if (e != hipSuccess) return hip_fail(e);
-        it = g_graphs.insert_or_assign(key, exec).first;
+        it = g_graphs.emplace(key, exec).first;
     }
     hipError_t e = hipGraphLaunch(it->second, s);
     return e == hipSuccess ? SPIN_OK : hip_fail(e);
@@ -1091,9 +1095,9 @@ const char *spin_strerror(int code) {
 void spin_release(void) {
     std::lock_guard<std::mutex> lk(g_mu);
     hipDeviceSynchronize();
-    for (auto &kv : g_graphs)
-        if (kv.second) hipGraphExecDestroy(kv.second);
+    for (auto &kv : g_graphs) hipGraphExecDestroy(kv.second);
     g_graphs.clear();
+    g_seen.clear();
     for (auto &kv : g_ws)
         if (kv.second.base) hipFree(kv.second.base);
     g_ws.clear();
