@@ -360,7 +360,8 @@ int64_t spin_plan_describe(int64_t n, int64_t lda, int64_t ldx, int64_t leaf,
 int64_t spin_plan_describe_spd(int64_t n, int64_t lda, int64_t ldx, int64_t leaf,
                                spin_plan_op *ops, int64_t cap, double *flops);
 /* The same for spin_invert_lu (kinds 0, 4 and 5; leaf <= 128), with its
- * workspace size in elements. */
+ * workspace size in elements.  *flops counts every product whole and 4/3 L^3
+ * per leaf; its kernels leave out the zero triangles, as traced flops do. */
 int64_t spin_plan_describe_lu(int64_t n, int64_t lda, int64_t ldx, int64_t leaf,
                               spin_plan_op *ops, int64_t cap, double *flops);
 int64_t spin_plan_ws_elems_lu(int64_t n, int64_t leaf);
@@ -370,7 +371,7 @@ int64_t spin_plan_ws_elems(int64_t n, int64_t leaf);
 typedef struct spin_trace_rec {
     char kernel[48];  /* kernel family and tile shape                           */
     double ms;        /* HIP-event time of the launch on its stream             */
-    double flops;     /* algorithmic flops of the launch                        */
+    double flops;     /* algorithmic flops of the launch, without zero triangles */
     double bytes;     /* algorithmic HBM bytes of the launch (operands + result) */
     int level;        /* recursion level (-1 outside the recursion)             */
 } spin_trace_rec;

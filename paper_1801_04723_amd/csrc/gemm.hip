@@ -1209,7 +1209,7 @@ hipError_t gemm_launch(const GemmProb *probs, int count, DType dt, hipStream_t s
         const double m = probs[q].m, n = probs[q].n, k = probs[q].k;
         // a lower-triangle product computes about m (m + tile) / 2 outputs
         flops += (probs[q].lower && probs[q].m == probs[q].n) ? k * m * (m + cfgs[n_live - 1].tile)
-                                                               : 2.0 * m * n * k;
+                                                               : product_flops(probs[q].m, probs[q].n, probs[q].k, probs[q].tri);
         bytes += es * (m * k + k * n + m * n + ((probs[q].beta != 0.0) ? m * n : 0.0));
         if (probs[q].DT != nullptr) bytes += es * m * n * (probs[q].lower ? 0.5 : 1.0);
     }

@@ -54,6 +54,14 @@ constexpr int kTriALower = 1;  // A[i][k] = 0 for k > i
 constexpr int kTriAUpper = 2;  // A[i][k] = 0 for k < i
 constexpr int kTriBLower = 4;  // B[k][j] = 0 for k < j
 constexpr int kTriBUpper = 8;  // B[k][j] = 0 for k > j
+// Operations of a product without those on the zero triangles of its operands
+// (square ones, as the LU schedule has them).
+inline double product_flops(int64_t m, int64_t n, int64_t k, int tri) {
+    const bool a = (tri & (kTriALower | kTriAUpper)) && m == k, b = (tri & (kTriBLower | kTriBUpper)) && n == k;
+    if (a && b) return (double)k * (k + 1) * (2.0 * k + 1) / 3.0;  // upper times lower
+    if (a || b) return (double)k * (k + 1) * (a ? n : m);
+    return 2.0 * m * n * k;
+}
 
 // One gemm_launch() call takes up to kMaxBatch independent products; products
 // that share a kernel configuration run in one grid (every workgroup finds
