@@ -128,6 +128,8 @@ __device__ inline void tri_range(int tri, int m0, int bm, int n0, int bn, int bk
     kt1 = max(kt0, (hi + bk - 1) / bk);
 }
 
+// Guarded path: every element loaded by itself, for products that have no
+// vector of A to load (fewer rows than one, or an empty reduction).
 template <int BM, int BN, int BK, int WM, int WN, typename T, int NG>
 __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
     constexpr int NT = 256;
@@ -164,31 +166,17 @@ __global__ void __launch_bounds__(256) gemm_kernel(GroupArgs<NG> g) {
 
     T ra[A_PT], rb[B_PT];
     auto gload = [&](int k0) {
-        const bool full = (m0 + BM <= M) && (n0 + BN <= N) && (k0 + BK <= K);
-        if (full) {
 #pragma unroll
-            for (int i = 0; i < A_PT; ++i) {
-                const int e = tid + NT * i, r = e % BM, c = e / BM;
-                ra[i] = A[(m0 + r) + (int64_t)(k0 + c) * lda];
-            }
+        for (int i = 0; i < A_PT; ++i) {
+            const int e = tid + NT * i, r = e % BM, c = e / BM;
+            const bool ok = (m0 + r < M) && (k0 + c < K);
+            ra[i] = ok ? A[(m0 + r) + (int64_t)(k0 + c) * lda] : T(0);
+        }
 #pragma unroll
-            for (int i = 0; i < B_PT; ++i) {
-                const int e = tid + NT * i, r = e % BK, c = e / BK;
-                rb[i] = B[(k0 + r) + (int64_t)(n0 + c) * ldb];
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < A_PT; ++i) {
-                const int e = tid + NT * i, r = e % BM, c = e / BM;
-                const bool ok = (m0 + r < M) && (k0 + c < K);
-                ra[i] = ok ? A[(m0 + r) + (int64_t)(k0 + c) * lda] : T(0);
-            }
-#pragma unroll
-            for (int i = 0; i < B_PT; ++i) {
-                const int e = tid + NT * i, r = e % BK, c = e / BK;
-                const bool ok = (k0 + r < K) && (n0 + c < N);
-                rb[i] = ok ? B[(k0 + r) + (int64_t)(n0 + c) * ldb] : T(0);
-            }
+        for (int i = 0; i < B_PT; ++i) {
+            const int e = tid + NT * i, r = e % BK, c = e / BK;
+            const bool ok = (k0 + r < K) && (n0 + c < N);
+            rb[i] = ok ? B[(k0 + r) + (int64_t)(n0 + c) * ldb] : T(0);
         }
     };
     auto sstore = [&](int buf) {
@@ -1163,11 +1151,11 @@ hipError_t launch_cfg_bf16(Cfg c, const GemmProb *probs, int count, hipStream_t 
 
 const char *cfg_name(Cfg c, DType dt) {
     static const char *names[4][3][3] = {
-        {{"gemm_f64_128x128_edge", "gemm_f64_128x128", "gemm_f64_128x128_ragged"},
-         {"gemm_f64_64x64_edge", "gemm_f64_64x64", "gemm_f64_64x64_ragged"},
+        {{"", "gemm_f64_128x128", "gemm_f64_128x128_ragged"},
+         {"", "gemm_f64_64x64", "gemm_f64_64x64_ragged"},
          {"gemm_f64_32x32_edge", "gemm_f64_32x32", "gemm_f64_32x32_ragged"}},
-        {{"gemm_f32_128x128_edge", "gemm_f32_128x128", "gemm_f32_128x128_ragged"},
-         {"gemm_f32_64x64_edge", "gemm_f32_64x64", "gemm_f32_64x64_ragged"},
+        {{"", "gemm_f32_128x128", "gemm_f32_128x128_ragged"},
+         {"", "gemm_f32_64x64", "gemm_f32_64x64_ragged"},
          {"gemm_f32_32x32_edge", "gemm_f32_32x32", "gemm_f32_32x32_ragged"}},
         {{"gemm_bf16_128x128_edge", "gemm_bf16_128x128", ""},
          {"gemm_bf16_64x64_edge", "gemm_bf16_64x64", ""},

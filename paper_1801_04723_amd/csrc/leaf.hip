@@ -1871,12 +1871,8 @@ int panel_width(int64_t L) {
 }
 
 hipError_t panel_launch(const PanelArgs &pa, hipStream_t s) {
-    const int L = pa.L;
-    if (L <= 256)
-        hipLaunchKernelGGL((leaf_panel<64, 1, 256>), dim3(1), dim3(256), 0, s, pa);
-    else if (L <= 512)
-        hipLaunchKernelGGL((leaf_panel<64, 1, 512>), dim3(1), dim3(512), 0, s, pa);
-    else if (L <= 1024)
+    const int L = pa.L;  // above 512
+    if (L <= 1024)
         hipLaunchKernelGGL((leaf_panel<32, 1, 1024>), dim3(1), dim3(1024), 0, s, pa);
     else
         hipLaunchKernelGGL((leaf_panel<16, 2, 1024>), dim3(1), dim3(1024), 0, s, pa);
