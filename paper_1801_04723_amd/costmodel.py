@@ -21,8 +21,8 @@ order 128 also more panels, each with an update product), so the leaf term
 grows with L.  The node term loses its deepest level each time L doubles, and
 those are the launch-bound levels.  The U-curve is the sum of the two.
 
-`calibrate()` measures both tables on the GPU (graph-replayed inversions for
-leaves and small nodes, standalone products for large nodes); `predict()` and
+`calibrate()` measures both tables on the GPU (repeated inversions for leaves
+and small nodes, standalone products for large nodes); `predict()` and
 `best_leaf()` are plain host arithmetic on them.
 """
 from __future__ import annotations
@@ -113,9 +113,13 @@ def calibrate(leaves=(32, 64, 128, 256, 512, 1024, 2048), hs=(32, 64, 128, 256, 
               large_h: int = 1024) -> Rates:
     """Measure t_leaf(L) and t_node(h) on the current GPU.
 
-    * t_leaf(L): spin_invert of an order-L matrix with leaf L (graph replay);
-    * t_node(h), h < large_h: t(2h, leaf h) - 2 t_leaf(h), both graph-replayed,
-      so the launch gaps inside a schedule are included;
+    * t_leaf(L): spin_invert of an order-L matrix with leaf L, calls in a row;
+    * t_node(h), h < large_h: t(2h, leaf h) - 2 t_leaf(h), so the launch gaps
+      inside a schedule are included.  Calls of fewer than ten launches (whole
+      leaves and their nodes among them) run as direct launches, the others as
+      graph replays like the inversions that are priced; in a row, with the GPU
+      behind the host, the kernels follow each other as closely either way (a
+      leaf of order 256 146 us direct, 149 replayed);
     * t_node(h), h >= large_h: the node's four launches as standalone products
       (a pair timed as one (2h x h x h) product, which has the same tile
       configuration at these sizes), launched back to back.

@@ -9,11 +9,11 @@
 // (alpha = -1, beta = 1, C0 == D), and the Newton residual R = I - A*X
 // (alpha = -1, add_identity).
 //
-// Kernel shape: 256 threads = 4 wave64s; a BM x BN output tile per workgroup,
-// split 2 x 2 into WM x WN wave tiles of 16 x 16 MFMA blocks.  K advances in
-// BK slabs staged global -> registers -> LDS with two LDS buffers, so the
-// global loads of slab k+1 are in flight while the matrix cores consume
-// slab k, with one barrier per slab.
+// Kernel shape: a BM x BN output tile per workgroup of four or eight wave64s,
+// split into WM x WN wave tiles of 16 x 16 MFMA blocks.  K advances in BK slabs
+// staged global -> registers -> LDS with two LDS buffers, so the global loads of
+// slab k+1 (and later ones, on the smaller tiles) are in flight while the matrix
+// cores consume slab k, with one barrier per slab.
 //
 // Matrix-core operands are issued transposed (B^T tile as the first operand,
 // A^T tile as the second), so each accumulator holds a 16 x 16 block of D^T:
@@ -767,9 +767,11 @@ __global__ void __launch_bounds__(64 * NW, NW / 2) gemm_bf16(GroupArgs<NG> g) {
 // slab is rounded and stored piece by piece between the matrix instructions of
 // the current one, from registers loaded an iteration earlier.
 //
-// What bounds it: the matrix cores at the rate that this card holds under
-// load; bf16x3 at 8192 x 8192 x 4096 reaches 1 145 TFLOP/s (a library BF16
-// product of order 4096: 1 124).  The 128 x 128 tile was bound by LDS: with an
+// What bounds it: no single unit.  bf16x3 keeps the matrix cores busy for 52 %
+// of the cycles and loses 9 % to LDS conflicts; with two waves on a SIMD and one
+// barrier per slab, LDS reads and conversions are covered in part.  It issues 1 145
+// TFLOP/s at 8192 x 8192 x 4096 (a library BF16 product of order 4096: 1 124).
+// The 128 x 128 tile was bound by LDS: with an
 // 80-byte pitch its reads took twice the cycles of its matrix instructions.
 // bf16x3 4096^3 488 -> 357 us, 8192 x 8192 x 4096 1 897 -> 1 441 us; plain
 // BF16 (the conversion of twice as many values per matrix instruction shows)

@@ -33,9 +33,11 @@
 //   and the input is copied into Z.
 //
 // Speculation: every kernel up to order 512 first tries the diagonal pivots
-// in 16-step blocks on the matrix cores, checks each choice exactly and falls
-// back to its search when a check fails (gj2d_any, gj_ahead, gj_blocked); the result is
-// the search's bit for bit either way.
+// (in 16-step blocks on the matrix cores, except leaf_duo), checks each choice
+// exactly and falls back to its search when a check fails (gj2d_any, gj_ahead,
+// gj_blocked); the result is the search's bit for bit either way.  In the blocked
+// kernels a pivot outside 2^-500 .. 2^501 behind a diagonal within 2^-400 ..
+// 2^401 fails its check too.
 #include <hip/hip_runtime.h>
 
 #include <cfloat>
@@ -1088,8 +1090,9 @@ __device__ __attribute__((always_inline)) inline bool gj_ahead(const LeafArgs &a
     constexpr auto kSteps = std::make_integer_sequence<int, 16>{};
     const int nblk = (L + 15) >> 4;
 
-    // for the two waves that need it
+    // for the two waves that need it (an FP32 entry is never far)
     auto divide = [&] {
+        if constexpr (sizeof(TI) == 4) return false;
         bool far = false;
 #pragma unroll
         for (int i = lane0; i < N; i += 64)

@@ -29,9 +29,9 @@ namespace {
 // above and left of the diagonal block, which step k leaves alone.  Wave w
 // holds the 16 rows 16 w .. 16 w + 15 in accumulators; panels pass through LDS.
 //
-// Bound by the chains and panels (about 9 000 cycles a block step), against a
-// column-at-a-time elimination and two substitution passes in LDS with two
-// barriers per column before: order 128 731 -> 46 us.
+// Bound by the chains and panels, one after the other (7 us a block step of eight
+// waves), against a column-at-a-time elimination and two substitution passes in
+// LDS with two barriers per column before: order 128 731 -> 59 us.
 
 // Pivots that are normal numbers with a normal reciprocal, which quotient
 // needs.  Blocks with another one (subnormal, above 2^1022, zero or not
