@@ -134,8 +134,13 @@ __global__ void __launch_bounds__(256) k_fill_zero(double *__restrict__ d, int64
 //               (|A|_F |X|_F) <= kNsTol (norms[2] = |R|^2, norms[0] = |A|^2; a
 //               NaN anywhere fails the test).
 // Three launches for each norm before (partials, sum, check): 14 mixed requests
-// of a batch spent 680 us on 70 norms, 230 us now; order 2048 12 to 17 us a
-// norm, 11 us now.
+// of a batch spent 680 us on 70 norms, 230 us now.  What bounds a small one is
+// latency: a round trip for the columns, which another XCD has just written, and
+// three for the hand-over.  Right behind the kernel that wrote the view, in a
+// graph, against three launches and a column at a time: order 64 5.8 -> 3.5 us,
+// 192 5.9 -> 4.3, 384 6.6 -> 5.0, 768 8.5 -> 7.1, 2048 12.0 -> 11.2, 8192 156 ->
+// 109; only 1024 lost, 6.7 -> 9.0.  With one column of a wave in flight 192 and 384
+// took 8.3 and 9.1 us.
 __device__ inline double block_sum(double s) {
     __shared__ double red[4];
 #pragma unroll
@@ -146,6 +151,22 @@ __device__ inline double block_sum(double s) {
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+// A lane's sum over N columns, stride elements apart, from row threadIdx % 64 on:
+// 16 loads are in flight whatever m is.
+template <int N>
+__device__ inline double frob_columns(const double *col, int64_t stride, int64_t m) {
+    double s[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) s[q] = 0.0;
+#pragma unroll(16 / N)
+    for (int64_t i = threadIdx.x & 63; i < m; i += 64)
+#pragma unroll
+        for (int q = 0; q < N; ++q) s[q] = fma(col[i + q * stride], col[i + q * stride], s[q]);
+    if constexpr (N == 4) return (s[0] + s[1]) + (s[2] + s[3]);
+    if constexpr (N == 2) return s[0] + s[1];
+    return s[0];
+}
+
 __global__ void __launch_bounds__(256) k_frob(AuxArgs<FrobItem> a) {
     __shared__ bool last;
     const int q = aux_member(a);
@@ -153,12 +174,15 @@ __global__ void __launch_bounds__(256) k_frob(AuxArgs<FrobItem> a) {
     const int b = (int)blockIdx.x - a.start[q], nb = it.blocks;
     const int64_t m = it.m, n = it.n;
     double s = 0.0;
-    // a wave takes a column, 64 rows at a time
-    for (int64_t c = b * 4 + (threadIdx.x >> 6); c < n; c += nb * 4) {
-        const double *col = it.src + c * it.ld;
-#pragma unroll 8
-        for (int64_t i = threadIdx.x & 63; i < m; i += 64) s = fma(col[i], col[i], s);
+    // a wave takes every 4 nb-th column, up to four at a time
+    const int64_t step = nb * 4, stride = step * it.ld;
+    int64_t c = b * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (; c + 3 * step < n; c += 4 * step) s += frob_columns<4>(it.src + c * it.ld, stride, m);
+    if (c + step < n) {
+        s += frob_columns<2>(it.src + c * it.ld, stride, m);
+        c += 2 * step;
     }
+    if (c < n) s += frob_columns<1>(it.src + c * it.ld, stride, m);
     s = block_sum(s);
     double *const partials = it.partials;
     unsigned *const counter = reinterpret_cast<unsigned *>(partials) - 2;
@@ -264,12 +288,12 @@ hipError_t transpose_f64(const double *src, int64_t lds, double *dst, int64_t ld
     return hipGetLastError();
 }
 
-// Blocks of a norm: one per 32 KB (16 loads a lane), at most kNormBlocks,
-// because counting a block takes about 20 ns, and at most one per column
-// quartet.
+// Blocks of a norm: one per 16 columns, four to a wave, or per 128 KB (64 loads a
+// lane) if that is more, at most kNormBlocks, because counting a block takes about
+// 20 ns, and at most one per column quartet.
 int frob_partials_count(int64_t m, int64_t n) {
-    const int64_t b = std::min<int64_t>({(m * n + 4095) / 4096, (n + 3) / 4, kNormBlocks});
-    return (int)std::max<int64_t>(b, 1);
+    const int64_t b = std::max<int64_t>((n + 15) / 16, (m * n + 16383) / 16384);
+    return (int)std::max<int64_t>(std::min<int64_t>({b, (n + 3) / 4, kNormBlocks}), 1);
 }
 
 hipError_t frob_counter_reset(int *status, hipStream_t s) {
