@@ -40,7 +40,9 @@
  *   Leaves     two further environment variables change how a leaf is
  *              eliminated but never its result: SPIN_NO_SPEC=1 runs the pivot
  *              search at every step instead of first trying the diagonal
- *              pivots and verifying them; SPIN_DUO_SPIN=<count> lowers the
+ *              pivots and verifying them (leaves with a diagonal entry beyond
+ *              2^+-400 divide in between; others search when a pivot leaves
+ *              2^+-500); SPIN_DUO_SPIN=<count> lowers the
  *              bound on each wait of a panel eliminated by two workgroups
  *              (a wait that runs out sends the panel to the one-workgroup
  *              search).  Both are read when a call is enqueued, and a graph
